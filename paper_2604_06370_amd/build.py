@@ -20,13 +20,18 @@ HIPCC = os.path.join(ROCM, "bin", "hipcc")
 ARCH = "gfx950"
 
 HOST_SOURCES = ["tree.cpp", "plan.cpp", "capi.cpp"]
-HIP_SOURCES = ["decode.hip", "prefill.hip", "kvcache.hip"]
+HIP_SOURCES = ["decode.hip", "prefill.hip", "prefill_stream.hip", "kvcache.hip"]
 
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function"]
 # Packed fp32 VALU instructions are kept out of the device code.
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-ffp-contract=fast", "-munsafe-fp-atomics"]
+
+# The pipelined prefill kernel keeps its accumulators in vector registers: the default puts every matrix
+# result of a kernel that may use more than 256 registers into accumulation registers, and the
+# scores then cost a move per value.
+FILE_FLAGS = {"prefill_stream.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _run(cmd, verbose):
@@ -52,7 +57,7 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
         if not os.path.exists(src):
             continue
         o = os.path.join(BUILD, s + ".o")
-        cmds.append([HIPCC, *HIP_FLAGS, "-c", src, "-o", o])
+        cmds.append([HIPCC, *HIP_FLAGS, *FILE_FLAGS.get(s, []), "-c", src, "-o", o])
         objs.append(o)
     jobs = jobs or min(8, os.cpu_count() or 1)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:

@@ -19,7 +19,9 @@ namespace fkvk {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -30,6 +32,10 @@ __device__ __forceinline__ f32x4 mfma32(const u32x4 &a, const u32x4 &b, const f3
 __device__ __forceinline__ f32x4 mfma16(const u32x2 &a, const u32x2 &b, const f32x4 &c) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), c,
                                                      0, 0, 0);
+}
+
+__device__ __forceinline__ f32x16 mfma32x32(const u32x4 &a, const u32x4 &b, const f32x16 &c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
 // Two fp32 -> packed bf16 pair (round to nearest even; v_cvt_pk_bf16_f32).
@@ -43,6 +49,11 @@ __device__ __forceinline__ u32x2 pack4(const f32x4 &x) {
     r.x = pack_bf16(x.x, x.y);
     r.y = pack_bf16(x.z, x.w);
     return r;
+}
+// Eight consecutive values of x from i0.
+__device__ __forceinline__ u32x4 pack8(const f32x16 &x, int i0) {
+    return u32x4{pack_bf16(x[i0], x[i0 + 1]), pack_bf16(x[i0 + 2], x[i0 + 3]), pack_bf16(x[i0 + 4], x[i0 + 5]),
+                 pack_bf16(x[i0 + 6], x[i0 + 7])};
 }
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -77,6 +88,13 @@ __device__ __forceinline__ float max_over_groups(float x) {
     const uint32_t v = __float_as_uint(y);
     const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
     return fmaxf(y, __uint_as_float((threadIdx.x & 16) ? b[0] : b[1]));
+}
+
+// Maximum over the two lane halves (lanes l and l^32).
+__device__ __forceinline__ float max_over_halves(float x) {
+    const uint32_t u = __float_as_uint(x);
+    const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
 }
 
 }  // namespace fkvk

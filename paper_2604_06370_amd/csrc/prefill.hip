@@ -1,13 +1,14 @@
-// ResidualAttention chunked prefill for gfx950 (Section 6 prefill kernel,
-// Algorithm 1 with a block of query rows).
+// ResidualAttention chunked prefill for gfx950: the entry point, and the kernel for RoPE on at
+// ranks 32 and 64 (Section 6 prefill kernel, Algorithm 1 with a block of query rows).  Every other
+// shape runs on the pipelined kernel of prefill_stream.hip, whose form of three tiles in flight does
+// not fit the registers (rank 32) or the LDS (rank 64) here; see the dispatch at the end.
 //
 // One workgroup of eight waves = (agent a, KV head h, block of 256 query rows); its rows
 // are (query token, query head of h), all of the same agent, so every 64-key tile of the
 // agent's keys is staged once in LDS and applied to all 256 rows:
-//   RoPE on, per tile: U^T = B_K^T C_K^T (MFMA), K_lora = RoPE_p(U) (rotate-half, fp32),
+//   per tile:          U^T = B_K^T C_K^T (MFMA), K_lora = RoPE_p(U) (rotate-half, fp32),
 //                      K = K_base + K_lora -> bf16, in place in LDS
 //   every wave, for its 32 rows:  S^T = K Q^T              (16x16x32 MFMA)
-//                                 RoPE off: S^T += C_K (B_K q)^T
 //                                 causal mask + online softmax
 //                                 O^T   += V^T P^T          (16x16x32 MFMA)
 //                                 acc_r^T += C_V^T P^T
@@ -27,8 +28,10 @@
 #include "internal.hpp"
 #include "lds_dma.hpp"
 #include "mfma.hpp"
+#include "prefill.hpp"
 
 using namespace fkvk;
+using namespace fkvp;
 
 namespace {
 
@@ -36,32 +39,7 @@ constexpr int D = 128;
 constexpr int PS = 16;
 constexpr int ROWS_PER_WAVE = 32;          // two 16-row tiles
 constexpr int TILE_KEYS = 64;              // four pages
-constexpr int kXcds = 8;
 constexpr float kNegInf = -INFINITY;
-
-struct PrefillArgs {
-    const uint16_t *q, *base_kv, *res_kv, *lora_b;
-    const int32_t *adapter_idx, *base_bt, *res_bt, *seq_lens, *q_indptr;
-    const float *rope_cos, *rope_sin;
-    uint16_t *out;
-    int32_t n_agents, hq, hkv, max_pages, blocks_per_agent_head;
-    float scale_log2;
-    int32_t rope_rows;  // positions the RoPE tables hold
-};
-
-
-// Rows of an agent's chunk that its query blocks do not reach (a max_q_per_agent below the
-// agent's row count) are written as NaN by the agent's last block, so the shortfall shows in
-// the output instead of leaving stale memory there.
-__device__ __forceinline__ void poison_unreached_rows(const PrefillArgs &p, int q0, int nq, int h, int g, int reach) {
-    const uint32_t nan2 = 0x7fc07fc0u;  // two bf16 quiet NaNs
-    for (int64_t i = threadIdx.x; i < (int64_t)(nq - reach) * g * 32; i += blockDim.x) {
-        const int64_t row = i / 32, c = i % 32;
-        const int tok = reach + (int)(row / g), j = (int)(row % g);
-        uint16_t *orow = p.out + ((int64_t)(q0 + tok) * p.hq + h * g + j) * 128;
-        *reinterpret_cast<u32x2 *>(orow + 4 * c) = u32x2{nan2, nan2};
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Streaming kernel.  A workgroup of eight waves holds 256 query rows, and 64-key tiles
@@ -119,7 +97,7 @@ struct StreamShape {
 };
 
 template <int R, int G, bool ROPE>
-__global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_stream_kernel(PrefillArgs p) {
+__global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(PrefillArgs p) {
     using S = StreamShape<R, ROPE>;
     constexpr int RT = S::RT;
     constexpr int RTX = RT > 0 ? RT : 1;
@@ -696,21 +674,14 @@ hipError_t launch_prefill(const PrefillArgs &pa, hipStream_t st, void *const *ev
     // timing events carry the kernel's own start and end timestamps (set by the launch)
     hipEvent_t e0 = ev ? static_cast<hipEvent_t>(ev[0]) : nullptr;
     hipEvent_t e1 = ev ? static_cast<hipEvent_t>(ev[1]) : nullptr;
-    hipExtLaunchKernelGGL((prefill_stream_kernel<R, G, ROPE>), dim3(grid), dim3(64 * kStreamWaves), 0, st, e0, e1, 0, pa);
+    hipExtLaunchKernelGGL((prefill_rebuild_kernel<R, G, ROPE>), dim3(grid), dim3(64 * kStreamWaves), 0, st, e0, e1, 0, pa);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return hipSuccess;
 }
 
 template <int G>
-hipError_t dispatch_prefill(int r, bool rope, const PrefillArgs &pa, hipStream_t st, void *const *ev) {
-    switch (r) {
-    case 0: return launch_prefill<0, G, false>(pa, st, ev);
-    case 8: return rope ? launch_prefill<8, G, true>(pa, st, ev) : launch_prefill<8, G, false>(pa, st, ev);
-    case 16: return rope ? launch_prefill<16, G, true>(pa, st, ev) : launch_prefill<16, G, false>(pa, st, ev);
-    case 32: return rope ? launch_prefill<32, G, true>(pa, st, ev) : launch_prefill<32, G, false>(pa, st, ev);
-    case 64: return rope ? launch_prefill<64, G, true>(pa, st, ev) : launch_prefill<64, G, false>(pa, st, ev);
-    default: return hipErrorInvalidValue;
-    }
+hipError_t dispatch_prefill(int r, const PrefillArgs &pa, hipStream_t st, void *const *ev) {
+    return r == 32 ? launch_prefill<32, G, true>(pa, st, ev) : launch_prefill<64, G, true>(pa, st, ev);
 }
 
 }  // namespace
@@ -751,14 +722,26 @@ extern "C" fkv_status fkv_residual_attention_prefill(const fkv_attn_args *a, voi
     pa.rope_rows = a->rope_cos ? a->rope_max_pos : 0;
     // query blocks per (agent, KV head); blocks past an agent's own chunk exit at once
     const bool rope = a->rope_cos != nullptr && a->r > 0;
-    const int tok_per_wg = kStreamRows / g;
     const int maxq = a->max_q_per_agent > 0 ? a->max_q_per_agent : a->n_q;
     if (maxq > a->n_q) return fkv::fail(FKV_ERR_INVALID, "fkv_residual_attention_prefill: max_q_per_agent > n_q");
-    pa.blocks_per_agent_head = (maxq + tok_per_wg - 1) / tok_per_wg;
+    // Which kernel and how many rows per workgroup:
+    //  - RoPE on at rank 64, and at rank 32 unless the grid is small: the rebuild kernel (the
+    //    pipelined one spills there: 4 agents x 2048 rows, 8B heads, rank 32: 7.5 ms against 15.5;
+    //    rank 64: 7.8 against over 20);
+    //  - else the pipelined kernel, with 128 rows per workgroup when 256 would occupy at most half of
+    //    the compute units (4 agents x 250 rows over 32K, 8B heads, rank 16, RoPE off: 112 workgroups
+    //    920 us, 224 workgroups 844 us, both before the copies went further ahead; now 620) and at
+    //    rank 64 (RoPE off), where eight waves spill (4 agents x 2048 rows: 8.4 -> 7.5 ms).
+    const int blocks256 = (int)(((int64_t)maxq * g + 255) / 256);
+    const bool few = (int64_t)a->n_agents * a->hkv * blocks256 <= kCus / 2;
+    const bool rebuild = rope && (a->r == 64 || (a->r == 32 && !few));
+    const bool rows128 = !rebuild && (few || a->r == 64);
+    pa.blocks_per_agent_head = blocks256 * (rows128 ? 2 : 1);
     pa.scale_log2 = a->scale * 1.4426950408889634f;
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    hipError_t e = g == 4 ? dispatch_prefill<4>(a->r, rope, pa, hs, a->timing_events)
-                          : dispatch_prefill<8>(a->r, rope, pa, hs, a->timing_events);
+    hipError_t e = !rebuild ? launch_stream(a->r, g, rope, rows128, pa, hs, a->timing_events)
+                   : g == 4 ? dispatch_prefill<4>(a->r, pa, hs, a->timing_events)
+                            : dispatch_prefill<8>(a->r, pa, hs, a->timing_events);
     if (e != hipSuccess)
         return fkv::fail(FKV_ERR_HIP, std::string("fkv_residual_attention_prefill: launch failed: ") + hipGetErrorString(e));
     return FKV_OK;

@@ -186,3 +186,17 @@ def test_understated_row_count_shows_as_nan_rows():
     pos = {int(x): i for i, x in enumerate(rows)}
     check_close("maxq covered rows", out[[pos[int(x)] for x in p["q_index"]]], ref)
     lw.close()
+
+
+@pytest.mark.parametrize("r,rope", [(0, False), (8, True), (16, False), (16, True), (32, False), (32, True), (64, False)])
+@pytest.mark.parametrize("n_agents", [3, 17])
+def test_prefill_row_block_sizes(r, rope, n_agents):
+    """Grids that fill at most half of the compute units run 128 query rows per workgroup, larger
+    ones 256 (17 agents x 8 KV heads): sequences ending around 64-key tile edges, chunks around
+    both row-block sizes (32 and 64 tokens of four heads), one agent without adapter."""
+    chunk = [1, 31, 32, 33, 63, 64, 65, 5, 100, 2, 16, 17, 48, 64, 1, 7, 3][:n_agents]
+    end = [64, 65, 127, 128, 129, 191, 192, 193, 200, 63, 64, 128, 130, 320, 257, 256, 66][:n_agents]
+    suffix = [e - 24 - c if e - 24 - c > 0 else 1 for e, c in zip(end, chunk)]
+    wl = W._build("pf-blocks", 77, 32, 8, 128, r, 16, [-1], [24], [0] * n_agents, suffix, chunk, {1} if r else set(), 0.05)
+    lw, g, ref = run_prefill(f"row-blocks r={r} rope={rope} agents={n_agents}", wl, rope)
+    lw.close()
