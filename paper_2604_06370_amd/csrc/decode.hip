@@ -842,7 +842,9 @@ __global__ __launch_bounds__(256, R >= 64 ? 1 : 2) void decode_split_kernel(Deco
 // other groups from the caches.  The B_K^T fragments of every slot of the item are built in
 // LDS once per workgroup.  Per page and slot s of the wave's group (matrix-core products,
 // fp32 accumulate):
-//   U^T   = B_K,s^T C_K,s^T                  16x16x16
+//   U^T   = B_K,s^T C_K,s^T                  16x16x16; two rank tiles at a time (rank 32, 64): 16x16x32
+// (a 16x16x32 product takes the matrix core as long as a 16x16x16 one: 64 agents over a 128K tree at
+// rank 32, 2339 -> 2243 us; 24 agents with 70B heads at rank 64, bound elsewhere, 361 us either way)
 //   K_lr  = RoPE_p(U)                        rotate-half pairs (i, i + 64) in one lane, fp32
 //   S^T  += K_lr Q^T                         16x16x32, kept for the slot's own rows (columns)
 template <int R, int G>
@@ -850,10 +852,11 @@ struct RopeShape {
     static constexpr int RT = (R + 15) / 16;                       // 16-wide rank tiles
     static constexpr int NSW = fkv::decode_rope_wave_agents(G, R); // agent slots of a wave
     static constexpr int MS = fkv::decode_rope_item_agents(G, R);  // agent slots of an item
-    static constexpr int BKT = MS * RT * 8 * 512;                  // (slot, tile, column tile) x 64 lanes x 8 B
+    static constexpr int KT = RT % 2 == 0 ? 2 : 1;                 // rank tiles of one rebuild product
+    static constexpr int BKT = MS * RT * 8 * 512;                  // (slot, tiles, column tile) x 64 lanes x 8 KT B
     static constexpr int BK_UNITS = MS * RT * 128;                 // (slot, rank pair, 8-dim chunk)
     static_assert(BKT <= 64 * 1024, "two workgroups per compute unit");
-    static_assert(BK_UNITS % 256 == 0 && NSW * G <= ROWS, "shape");
+    static_assert(BK_UNITS % 256 == 0 && NSW * G <= ROWS && (KT == 2 || RT == 1), "shape");
 };
 
 template <int R, int G>
@@ -861,7 +864,7 @@ __global__ __launch_bounds__(256, 2) void decode_rope_kernel(DecodeArgs p) {
     static_assert(R > 0, "RoPE decode needs a residual");
     using S = RopeShape<R, G>;
     using RowsT = Rows<R>;
-    constexpr int RT = S::RT, NSW = S::NSW, MS = S::MS;
+    constexpr int RT = S::RT, NSW = S::NSW, MS = S::MS, KT = S::KT;
     constexpr int RTX = RowsT::RTX;
     // B_K^T fragments for the launch; at the end the merge area of the wave copies
     __shared__ __attribute__((aligned(16))) u32x2 bkt[cmax(S::BKT, merge_lds_bytes(R)) / 8];
@@ -941,7 +944,8 @@ __global__ __launch_bounds__(256, 2) void decode_rope_kernel(DecodeArgs p) {
     // B_K^T fragments of the item's slots for head h, built in LDS in rounds of four units: unit
     // (slot, rank pair, 8-dim chunk) loads ranks 2q and 2q + 1 over 8 dims (ranks past R and
     // slots without adapter: zero); lane (c, gg) of fragment (slot, tile t, column tile mt)
-    // holds B_K[16t + 4gg + j][16mt + c], j < 4, as two words of rank pairs
+    // holds B_K[16t + 4gg + j][16mt + c], j < 4, as two words of rank pairs; with KT == 2 the words
+    // of tiles t and t + 1 lie side by side, the operand of one 16x16x32 product
     {
         const int64_t n = (int64_t)hkv * D;
         uint32_t *bw = reinterpret_cast<uint32_t *>(bkt);
@@ -975,7 +979,8 @@ __global__ __launch_bounds__(256, 2) void decode_rope_kernel(DecodeArgs p) {
                     const int i = 8 * c8 + e, mt = i / 16, c = i % 16;
                     const uint32_t a = (e & 1) ? (lw[e >> 1] >> 16) : (lw[e >> 1] & 0xffffu);
                     const uint32_t b = (e & 1) ? (hw[e >> 1] >> 16) : (hw[e >> 1] & 0xffffu);
-                    bw[((((sl * RT + t) * 8 + mt) * 64) + c + 16 * gg) * 2 + j2] = a | (b << 16);
+                    const int frag = (((sl * RT + t) / KT * 8 + mt) * 64) + c + 16 * gg;
+                    bw[(frag * KT + t % KT) * 2 + j2] = a | (b << 16);
                 }
             }
         }
@@ -1086,9 +1091,17 @@ __global__ __launch_bounds__(256, 2) void decode_rope_kernel(DecodeArgs p) {
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         u[j] = f32x4{0, 0, 0, 0};
+                        if constexpr (KT == 2) {
+                            const u32x4 *bk4 = reinterpret_cast<const u32x4 *>(bkt);
 #pragma unroll
-                        for (int t = 0; t < RT; ++t)
-                            u[j] = mfma16(bkt[((slot * RT + t) * 8 + mts[j]) * 64 + lane], cfrag(s, t, true), u[j]);
+                            for (int t = 0; t < RT; t += 2) {
+                                const u32x2 c0 = cfrag(s, t, true), c1 = cfrag(s, t + 1, true);
+                                u[j] = mfma32(bk4[((slot * RT + t) / 2 * 8 + mts[j]) * 64 + lane],
+                                              u32x4{c0.x, c0.y, c1.x, c1.y}, u[j]);
+                            }
+                        } else {
+                            u[j] = mfma16(bkt[(slot * 8 + mts[j]) * 64 + lane], cfrag(s, 0, true), u[j]);
+                        }
                     }
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
