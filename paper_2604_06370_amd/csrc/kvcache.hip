@@ -14,6 +14,7 @@
 // plain [ps][d] (K), [d][ps] (V), [ps][r] (C_K) and [r][ps] (C_V).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 
 #include "internal.hpp"
@@ -62,13 +63,17 @@ __device__ __forceinline__ int c_slot(int64_t e, int ps, int r) {
     return e < (int64_t)ps * r ? (int)(e / r) : (int)((e - (int64_t)ps * r) % ps);
 }
 
+constexpr int kCopyParts = 16;  // workgroups per page copy at most
+
 struct CopyArgs {
     const fkv_page_copy *copies;
     uint16_t *base_kv, *res_kv;
     int32_t hkv, d, r, ps;
 };
 
-// One workgroup per copy.  Each thread moves 16-byte chunks: in both pools' layouts every
+// blockIdx.x names the copy; the gridDim.y workgroups of a copy take its 16-byte chunks in turn (one
+// chunk per thread where the page has enough of them: a copy is a chain of one load and one store,
+// so a page on one workgroup spent sixteen memory latencies at eight KV heads).  In both pools' layouts every
 // chunk of 8 values holds tokens of at most four consecutive slots, so a chunk whose slots are
 // all below n_valid is copied whole, one with none is skipped, and one that straddles n_valid
 // (a value chunk of four tokens, or an rCache chunk) is copied value by value.
@@ -76,7 +81,8 @@ template <typename SlotOf>
 __device__ __forceinline__ void copy_chunks(const uint16_t *src, uint16_t *dst, int64_t elems, int n_valid,
                                             SlotOf slot_of) {
     const int64_t chunks = elems / 8;
-    for (int64_t c = threadIdx.x; c < chunks; c += blockDim.x) {
+    const int first = (int)(blockIdx.y * blockDim.x + threadIdx.x), step = (int)(gridDim.y * blockDim.x);
+    for (int64_t c = first; c < chunks; c += step) {
         int lo = 1 << 30, hi = -1;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -92,27 +98,32 @@ __device__ __forceinline__ void copy_chunks(const uint16_t *src, uint16_t *dst, 
                 if (slot_of(8 * c + e) < n_valid) dst[8 * c + e] = src[8 * c + e];
         }
     }
-    for (int64_t e = chunks * 8 + threadIdx.x; e < elems; e += blockDim.x)
+    for (int64_t e = chunks * 8 + first; e < elems; e += step)
         if (slot_of(e) < n_valid) dst[e] = src[e];
 }
 
 __global__ __launch_bounds__(256) void page_copy_kernel(CopyArgs a) {
     const fkv_page_copy c = a.copies[blockIdx.x];
     const int n_valid = c.n_valid;
+    const int first = (int)(blockIdx.y * blockDim.x + threadIdx.x), step = (int)(gridDim.y * blockDim.x);
     if (c.pool == FKV_POOL_BASE) {
         const int64_t blk = (int64_t)a.ps * a.d;
         const int64_t page = 2 * a.hkv * blk;
         const uint16_t *src = a.base_kv + (int64_t)c.src * page;
         uint16_t *dst = a.base_kv + (int64_t)c.dst * page;
         const int hkv = a.hkv, ps = a.ps, d = a.d;
-        if (blk % 8 == 0) {
+        if (ps == 16 && d == 128) {
+            copy_chunks(src, dst, page, n_valid, [=](int64_t e) {
+                return (int)(e >> 11) >= hkv ? v_slot(e & 2047, 16, 128) : k_slot(e & 2047, 16, 128);
+            });
+        } else if (blk % 8 == 0) {
             // chunks never straddle a block: K blocks first (hkv of them), then V blocks
             copy_chunks(src, dst, page, n_valid, [=](int64_t e) {
                 const int64_t within = e % blk;
                 return (e / blk) >= hkv ? v_slot(within, ps, d) : k_slot(within, ps, d);
             });
         } else {
-            for (int64_t e = threadIdx.x; e < page; e += blockDim.x) {
+            for (int64_t e = first; e < page; e += step) {
                 const int64_t within = e % blk;
                 const int slot = (e / blk) >= hkv ? v_slot(within, ps, d) : k_slot(within, ps, d);
                 if (slot < n_valid) dst[e] = src[e];
@@ -126,7 +137,7 @@ __global__ __launch_bounds__(256) void page_copy_kernel(CopyArgs a) {
         if (ps == 16) {
             copy_chunks(src, dst, page, n_valid, [=](int64_t e) { return c_slot(e, ps, r); });
         } else {
-            for (int64_t e = threadIdx.x; e < page; e += blockDim.x)
+            for (int64_t e = first; e < page; e += step)
                 if (c_slot(e, ps, r) < n_valid) dst[e] = src[e];
         }
     }
@@ -138,65 +149,87 @@ struct ScatterArgs {
     const uint16_t *k_src, *v_src, *ck_src, *cv_src;
     uint16_t *base_kv, *res_kv;
     int32_t hkv, d, r, ps;
+    bool aligned16;  // K and V sources
 };
 
-// Page size 16, head dim 128: one workgroup per page the range [pos0, pos0 + n) touches.  Every
-// 16-byte chunk of the fragment-ordered blocks is formed in registers from the source rows and
-// stored whole: a K chunk is 8 dims of one token (two 8-byte pieces of its row); a V chunk is 2
-// dims of four consecutive tokens and an rCache chunk 4 ranks of one token (C_K) and one rank of
-// four tokens (C_V), so chunks whose tokens are only partly in the range are written value by
-// value (slots outside the range, and the rank padding of r = 8, keep their bits).
+// Page size 16, head dim 128: one workgroup per KV head and page that the range [pos0, pos0 + n)
+// touches, and one more per page for the rCache rows.  A workgroup's 16 token rows of K and V come
+// into LDS with one 16-byte load per thread and pool (row by row where a source is not aligned to 16
+// bytes), then every thread forms one 16-byte chunk of each fragment-ordered block and stores it
+// whole: a K chunk is 8 dims of one token, a V chunk 2 dims of four consecutive tokens and an rCache
+// chunk 4 ranks of one token (C_K) and one rank of four tokens (C_V), so chunks whose tokens are only
+// partly in the range are written value by value (slots outside the range, and the rank padding of
+// r = 8, keep their bits).  LDS rows are 8 values longer than the head: the four token groups of a V
+// chunk then read different banks.
+// Bound by latency: an agent's call has tens of pages, so what counts is the chain of one workgroup.
+// One workgroup per page walked through the heads, eight chunks of each kind per thread at eight KV
+// heads, V value by value from memory (page copies of eight forks and eight calls of 300 to 700
+// tokens at eight KV heads: 169 -> 94 us, what is left is mostly the nine calls' host time).
 __global__ __launch_bounds__(256) void scatter_page_kernel(ScatterArgs a) {
-    constexpr int PS = 16, D = 128;
+    constexpr int PS = 16, D = 128, ROW = D + 8;
+    __shared__ __attribute__((aligned(16))) uint16_t s_k[PS * ROW], s_v[PS * ROW];
     const int64_t first_page = a.pos0 / PS;
     const int64_t lp = first_page + blockIdx.x;
     const int64_t s0 = lp * PS;  // position of slot 0 of this page
     const int t_lo = (int)max<int64_t>(0, a.pos0 - s0), t_hi = (int)min<int64_t>(PS, a.pos0 + a.n - s0);
     auto row = [&](int t) { return s0 + t - a.pos0; };  // source row of slot t
-    const int hkv = a.hkv;
-    if (a.k_src) {
-        uint16_t *pg = a.base_kv + (int64_t)a.bt_base[lp] * 2 * hkv * PS * D;
-        // K: chunk (head, quarter q, lane L = t + 16 g) = dims 32q + 4g + 0..3 and 32q + 16 + 4g + 0..3 of token t
-        for (int c = threadIdx.x; c < hkv * 4 * 64; c += blockDim.x) {
-            const int hh = c / 256, q = (c / 64) % 4, L = c % 64;
-            const int t = L % 16, g = L / 16;
-            if (t < t_lo || t >= t_hi) continue;
-            const uint16_t *src = a.k_src + (row(t) * hkv + hh) * D + 32 * q + 4 * g;
-            const u32x2 lo = ldg64(src), hi = ldg64(src + 16);
-            *reinterpret_cast<u32x4 *>(pg + (int64_t)hh * PS * D + q * 512 + L * 8) = u32x4{lo.x, lo.y, hi.x, hi.y};
-        }
-        // V: chunk (head, quarter q, lane L = c + 16 tg) = dim 32q + c of tokens 4tg + 0..3, then dim 32q + 16 + c
-        uint16_t *pv = pg + (int64_t)hkv * PS * D;
-        for (int c = threadIdx.x; c < hkv * 4 * 64; c += blockDim.x) {
-            const int hh = c / 256, q = (c / 64) % 4, L = c % 64;
-            const int dc = L % 16, tg = L / 16;
-            const int ta = 4 * tg, tb = ta + 4;
-            if (tb <= t_lo || ta >= t_hi) continue;
-            uint16_t *dst = pv + (int64_t)hh * PS * D + q * 512 + L * 8;
-            if (ta >= t_lo && tb <= t_hi) {
-                uint16_t v[8];
+    const int hkv = a.hkv, hh = blockIdx.y;
+    if (a.k_src && hh < hkv) {
+        uint16_t *pk = a.base_kv + ((int64_t)a.bt_base[lp] * 2 * hkv + hh) * (PS * D), *pv = pk + (int64_t)hkv * PS * D;
+        {
+            const int t = threadIdx.x / 16, c = threadIdx.x % 16;
+            u32x4 k = {0, 0, 0, 0}, v = {0, 0, 0, 0};
+            if (t >= t_lo && t < t_hi) {
+                const int64_t at = (row(t) * hkv + hh) * D + 8 * c;
+                if (a.aligned16) {
+                    k = ldg128(a.k_src + at);
+                    v = ldg128(a.v_src + at);
+                } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint16_t *src = a.v_src + (row(ta + i) * hkv + hh) * D + 32 * q + dc;
-                    v[i] = src[0];
-                    v[4 + i] = src[16];
-                }
-                u32x4 w;
-                w.x = v[0] | ((uint32_t)v[1] << 16);
-                w.y = v[2] | ((uint32_t)v[3] << 16);
-                w.z = v[4] | ((uint32_t)v[5] << 16);
-                w.w = v[6] | ((uint32_t)v[7] << 16);
-                *reinterpret_cast<u32x4 *>(dst) = w;
-            } else {
-                for (int i = 0; i < 4; ++i) {
-                    const int t = ta + i;
-                    if (t < t_lo || t >= t_hi) continue;
-                    const uint16_t *src = a.v_src + (row(t) * hkv + hh) * D + 32 * q + dc;
-                    dst[i] = src[0];
-                    dst[4 + i] = src[16];
+                    for (int i = 0; i < 4; ++i) {
+                        k[i] = a.k_src[at + 2 * i] | ((uint32_t)a.k_src[at + 2 * i + 1] << 16);
+                        v[i] = a.v_src[at + 2 * i] | ((uint32_t)a.v_src[at + 2 * i + 1] << 16);
+                    }
                 }
             }
+            *reinterpret_cast<u32x4 *>(&s_k[t * ROW + 8 * c]) = k;
+            *reinterpret_cast<u32x4 *>(&s_v[t * ROW + 8 * c]) = v;
         }
+        __syncthreads();
+        const int q = threadIdx.x / 64, L = threadIdx.x % 64;
+        {
+            // K: chunk (quarter q, lane L = t + 16 g) = dims 32q + 4g + 0..3 and 32q + 16 + 4g + 0..3 of token t
+            const int t = L % 16, g = L / 16;
+            if (t >= t_lo && t < t_hi) {
+                const uint16_t *src = &s_k[t * ROW + 32 * q + 4 * g];
+                const u32x2 lo = ldg64(src), hi = ldg64(src + 16);
+                *reinterpret_cast<u32x4 *>(pk + q * 512 + L * 8) = u32x4{lo.x, lo.y, hi.x, hi.y};
+            }
+        }
+        // V: chunk (quarter q, lane L = c + 16 tg) = dim 32q + c of tokens 4tg + 0..3, then dim 32q + 16 + c
+        const int ta = 4 * (L / 16);
+        uint16_t v[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint16_t *src = &s_v[(ta + i) * ROW + 32 * q + L % 16];
+            v[i] = src[0];
+            v[4 + i] = src[16];
+        }
+        uint16_t *dst = pv + q * 512 + L * 8;
+        if (ta >= t_lo && ta + 4 <= t_hi) {
+            u32x4 w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = v[2 * i] | ((uint32_t)v[2 * i + 1] << 16);
+            *reinterpret_cast<u32x4 *>(dst) = w;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (ta + i < t_lo || ta + i >= t_hi) continue;
+                dst[i] = v[i];
+                dst[4 + i] = v[4 + i];
+            }
+        }
+        return;
     }
     if (a.ck_src && a.r > 0) {
         const int r = a.r, rt = (r + 15) / 16;
@@ -534,7 +567,9 @@ fkv_status fkv_page_copy_launch(const fkv_page_copy *copies_dev, int32_t n, void
     if (n == 0) return FKV_OK;
     if (!base_kv || (r > 0 && !res_kv)) return fkv::fail(FKV_ERR_INVALID, "fkv_page_copy_launch: pool pointer missing");
     CopyArgs a{copies_dev, static_cast<uint16_t *>(base_kv), static_cast<uint16_t *>(res_kv), hkv, d, r, page_size};
-    hipLaunchKernelGGL(page_copy_kernel, dim3(n), dim3(256), 0, static_cast<hipStream_t>(stream), a);
+    const int64_t chunks = (2LL * hkv * page_size * d + 7) / 8;  // of a base page, the larger of the two as a rule
+    const unsigned parts = (unsigned)std::min<int64_t>(kCopyParts, (chunks + 255) / 256);
+    hipLaunchKernelGGL(page_copy_kernel, dim3(n, parts), dim3(256), 0, static_cast<hipStream_t>(stream), a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fkv::fail(FKV_ERR_HIP, std::string("fkv_page_copy_launch: ") + hipGetErrorString(e));
     return FKV_OK;
@@ -557,10 +592,14 @@ fkv_status fkv_scatter_tokens(const int32_t *bt_base, const int32_t *bt_res, int
     ScatterArgs a{bt_base, bt_res, pos0, n,
                   static_cast<const uint16_t *>(k_src), static_cast<const uint16_t *>(v_src),
                   static_cast<const uint16_t *>(ck_src), static_cast<const uint16_t *>(cv_src),
-                  static_cast<uint16_t *>(base_kv), static_cast<uint16_t *>(res_kv), hkv, d, r, page_size};
-    if (page_size == 16 && d == 128) {
+                  static_cast<uint16_t *>(base_kv), static_cast<uint16_t *>(res_kv), hkv, d, r, page_size,
+                  ((reinterpret_cast<uintptr_t>(k_src) | reinterpret_cast<uintptr_t>(v_src)) & 15) == 0};
+    if (page_size == 16 && d == 128 && hkv < 65535) {
         const int64_t pages = (pos0 + n - 1) / 16 - pos0 / 16 + 1;
-        hipLaunchKernelGGL(scatter_page_kernel, dim3((unsigned)pages), dim3(256), 0, static_cast<hipStream_t>(stream), a);
+        // the rCache rows' workgroups follow those of the KV heads
+        const unsigned parts = (unsigned)((k_src ? hkv : 0) + (ck_src && r > 0 ? 1 : 0));
+        if (parts == 0) return FKV_OK;
+        hipLaunchKernelGGL(scatter_page_kernel, dim3((unsigned)pages, parts), dim3(256), 0, static_cast<hipStream_t>(stream), a);
     } else {
         hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)n), dim3(256), 0, static_cast<hipStream_t>(stream), a);
     }

@@ -86,3 +86,29 @@ def test_page_copies_move_exactly_the_valid_slots(hkv, r):
     rt.page_copy(copies, base_d, res_d, hkv, D, r, PS)
     assert np.array_equal(_host(base_d), exp_b)
     assert np.array_equal(_host(res_d), exp_r)
+
+
+@pytest.mark.parametrize("shift", [4, 8])
+@pytest.mark.parametrize("hkv,pos0,n", [(1, 15, 2), (8, 3, 29)])
+def test_scatter_sources_at_any_alignment(hkv, pos0, n, shift):
+    """K and V rows that start 8 or 16 bytes into an allocation give the bits that rows of their own
+    allocation give; K / V alone and rCache rows alone write what both together write."""
+    r, npages = 16, 4
+    g = torch.Generator(device="cuda").manual_seed(hkv + n)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    k, v, ck, cv = rnd(n, hkv, D), rnd(n, hkv, D), rnd(n, r), rnd(n, r)
+    bt = torch.randperm(npages, generator=g, device="cuda").int()
+    base, res = rnd(npages, 2, hkv, PS * D), rnd(npages, 512)
+    b1, r1, b2, r2 = base.clone(), res.clone(), base.clone(), res.clone()
+    rt.scatter_tokens(bt, bt, pos0, k, v, ck, cv, b1, r1, hkv, D, r, PS)
+    moved = []
+    for t in (k, v):
+        m = torch.empty(t.numel() + shift, dtype=t.dtype, device="cuda")[shift:].view_as(t)
+        m.copy_(t)
+        moved.append(m)
+    assert moved[0].data_ptr() % 16 == (8 if shift == 4 else 0)
+    rt.scatter_tokens(bt, None, pos0, *moved, None, None, b2, r2, hkv, D, r, PS)
+    assert np.array_equal(_host(r2.view(torch.int16)), _host(res.view(torch.int16)))
+    rt.scatter_tokens(None, bt, pos0, None, None, ck, cv, b2, r2, hkv, D, r, PS)
+    assert np.array_equal(_host(b1.view(torch.int16)), _host(b2.view(torch.int16)))
+    assert np.array_equal(_host(r1.view(torch.int16)), _host(r2.view(torch.int16)))
