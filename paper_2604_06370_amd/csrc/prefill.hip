@@ -48,15 +48,12 @@ constexpr float kNegInf = -INFINITY;
 // V block.  One barrier per tile hands a buffer over: every wave has waited (by count)
 // for its copies of the tile, and every wave has finished reading the buffer that the
 // copies issued after the barrier overwrite.
-//  - RoPE off: the key residual folds into the queries (S^T += C_K (B_K q)^T), so the
-//    stored blocks are used as they are; three buffers, copies two tiles ahead.
-//  - RoPE on: a tile also carries the cos/sin rows of its pages' first positions (each
-//    wave copies the 8 + 8 values per lane group that its rebuild uses); the rotation
-//    angle of token t of a page starting at p0 comes from those rows and the rows of
-//    positions 0..15 (kept in LDS for the launch) by angle addition.  Three buffers up to
-//    rank 32, two at rank 64 (copies one tile ahead).  After a tile has landed each wave rebuilds half of one page's keys
-//    in place (U^T = B_K^T C_K^T on the matrix cores, rotated, added to K_base) and a
-//    second barrier publishes the rebuilt tile.
+// A tile also carries the cos/sin rows of its pages' first positions (each wave copies the 8 + 8
+// values per lane group that its rebuild uses); the rotation angle of token t of a page starting at
+// p0 comes from those rows and the rows of positions 0..15 (kept in LDS for the launch) by angle
+// addition.  Three buffers at rank 32, two at rank 64 (copies one tile ahead).  After a tile has
+// landed each wave rebuilds half of one page's keys in place (U^T = B_K^T C_K^T on the matrix
+// cores, rotated, added to K_base) and a second barrier publishes the rebuilt tile.
 //
 // Buffer layout (bytes): K blocks [page][4 KB], V blocks [page][4 KB], rCache pages as
 // [rank tile][page][1 KB] (four pages of one rank tile are 1 KB apart).  All are stored
@@ -69,38 +66,38 @@ constexpr float kLazyRescale = 8.f;
 constexpr int kStreamWaves = 8;
 constexpr int kStreamRows = kStreamWaves * ROWS_PER_WAVE;
 
-template <int R, bool ROPE>
-struct StreamShape {
-    static constexpr int NBUF = (ROPE && R > 32) ? 2 : 3;  // ring buffers (copies NBUF - 1 tiles ahead)
+template <int R>
+struct RebuildShape {
+    static_assert(R == 32 || R == 64, "the ranks this kernel serves");
+    static constexpr int NBUF = R > 32 ? 2 : 3;  // ring buffers (copies NBUF - 1 tiles ahead)
     // Tile reads the compiler schedules (rank 64: 15.6 instead of 16.6 ms at 70B heads,
     // 8 x 1024 rows) or explicit ones that wait for themselves (below: no gain, 22.6 vs
     // 23.0 ms at 16 x 2048 rows, 8B heads)
     static constexpr bool CV = R >= 64;
-    static constexpr int RT = R == 0 ? 0 : (R + 15) / 16;
-    static constexpr int SBK_BYTES = ROPE ? RT * 8 * 64 * 8 : 0;  // B_K^T fragments (RoPE on)
+    static constexpr int RT = R / 16;
+    static constexpr int SBK_BYTES = RT * 8 * 64 * 8;  // B_K^T fragments
     static constexpr int K_OFF = 0;
     static constexpr int V_OFF = 4 * 4096;
     static constexpr int C_OFF = 8 * 4096;
     // RoPE on: table rows [page][half][cos m, cos m + 1, sin m, sin m + 1][1 KB], m = 2 half
     static constexpr int T_OFF = C_OFF + 4 * RT * 1024;
     // RoPE on: [page pw][half][cos, sin][frequency tile j][lane group] 16 B
-    static constexpr int BUF_BYTES = T_OFF + (ROPE ? 4 * 2 * 256 : 0);
-    static constexpr int SBV_BYTES = R > 0 ? R * D * 4 : 16;
-    static constexpr int SACC_BYTES = R > 0 ? kStreamRows * R * 4 : 16;
+    static constexpr int BUF_BYTES = T_OFF + 4 * 2 * 256;
+    static constexpr int SBV_BYTES = R * D * 4;
+    static constexpr int SACC_BYTES = kStreamRows * R * 4;
     static constexpr int EPI_BYTES = SBV_BYTES + SACC_BYTES;
     static constexpr int RING_BYTES = NBUF * BUF_BYTES;
     static constexpr int MAIN_BYTES = RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES;
     // RoPE on: cos then sin of positions 0..15 in the table's own order ([tile m][lane] 16 B)
-    static constexpr int COLT_BYTES = ROPE ? 2 * 4096 : 0;
+    static constexpr int COLT_BYTES = 2 * 4096;
     static constexpr int LDS_BYTES = MAIN_BYTES + SBK_BYTES + COLT_BYTES;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of one workgroup");
 };
 
-template <int R, int G, bool ROPE>
+template <int R, int G>
 __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(PrefillArgs p) {
-    using S = StreamShape<R, ROPE>;
+    using S = RebuildShape<R>;
     constexpr int RT = S::RT;
-    constexpr int RTX = RT > 0 ? RT : 1;
     constexpr int TPW = kStreamRows / G;
     __shared__ __attribute__((aligned(16))) u32x4 lds[S::LDS_BYTES / 16];
     float *sBV = reinterpret_cast<float *>(lds);
@@ -121,7 +118,7 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
     if (tok_begin >= nq) return;
     const int L = p.seq_lens[a];
     const int P0 = L - nq;  // position of the chunk's first query
-    const int ad = R > 0 ? p.adapter_idx[a] : -1;
+    const int ad = p.adapter_idx[a];
 
     const int lane = threadIdx.x & 63;
     const int wave = uniform(threadIdx.x >> 6);
@@ -132,8 +129,8 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
     const int last_pos = P0 + (tok_begin + TPW < nq ? tok_begin + TPW : nq) - 1;
     const int n_tiles = last_pos / TILE_KEYS + 1;
     const int32_t *btb = p.base_bt + (int64_t)a * p.max_pages;
-    const int32_t *btr = R > 0 ? p.res_bt + (int64_t)a * p.max_pages : nullptr;
-    const bool use_res = R > 0 && ad >= 0;
+    const int32_t *btr = p.res_bt + (int64_t)a * p.max_pages;
+    const bool use_res = ad >= 0;
 
     // This wave copies page pw of every tile: its K block and rCache page (waves 0..3) or
     // its V block (waves 4..7).
@@ -157,7 +154,7 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
         return (LdsU32x4 *)(lds + (tile % S::NBUF) * (S::BUF_BYTES / 16));
     };
     // RoPE tables (rope_rows positions of D / 2 floats each)
-    const int rope_bytes = ROPE ? p.rope_rows * (D / 2) * 4 : 0;
+    const int rope_bytes = p.rope_rows * (D / 2) * 4;
     const i32x4 rope_rc = block_rsrc(reinterpret_cast<uint64_t>(p.rope_cos), rope_bytes);
     const i32x4 rope_rs = block_rsrc(reinterpret_cast<uint64_t>(p.rope_sin), rope_bytes);
     // this wave's copies of tile `tile` (page 4 tile + pw)
@@ -175,7 +172,7 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
                 for (int t = 0; t < RT; ++t) lds_dma16(rc, lane * 16 + t * 1024, b + (S::C_OFF + (t * 4 + pw) * 1024) / 16);
             }
         }
-        if constexpr (ROPE && R > 0) {
+        {
             if (use_res) {
                 // cos and sin at the first position of page pw for the frequencies this wave's
                 // rebuild uses: lane 4j + g (< 8) copies the 16 bytes that lane group g holds in
@@ -216,41 +213,11 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
             qf[nt][kk] = v;
         }
     }
-    // W^T = (B_K q)^T per row tile and rank tile: the residual key term of row j is
-    // (B_K q_j) . c_p, one extra contraction over the rank
-    u32x2 wq[2][RTX];
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int t = 0; t < RTX; ++t) wq[nt][t] = u32x2{0, 0};
-    if constexpr (R > 0 && !ROPE) {
-        if (use_res) {
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-                for (int t = 0; t < RT; ++t) {
-                    f32x4 acc = {0, 0, 0, 0};
-                    const int rho = 16 * t + col;
-                    const uint16_t *bk = p.lora_b + (int64_t)ad * 2 * R * n + (int64_t)(rho < R ? rho : 0) * n + (int64_t)h * D;
-#pragma unroll
-                    for (int kk = 0; kk < 4; ++kk) {
-                        u32x4 av = {0, 0, 0, 0};
-                        if (rho < R) {
-                            const u32x2 lo = ldg64(bk + 32 * kk + 4 * grp);
-                            const u32x2 hi = ldg64(bk + 32 * kk + 16 + 4 * grp);
-                            av = u32x4{lo.x, lo.y, hi.x, hi.y};
-                        }
-                        acc = mfma32(av, qf[nt][kk], acc);
-                    }
-                    wq[nt][t] = pack4(acc);
-                }
-        }
-    }
     // RoPE on: B_K^T fragments of the agent's adapter (lane holds B_K[16t + 4grp + i][h*D +
     // 16mt + col]) in LDS for the whole launch; this wave rebuilds u tiles 2 half, 2 half + 1
     // and their rotation partners + 4 of page pw, with the table rows of frequency tiles
     // 2 half + j, loaded one tile ahead
-    if constexpr (ROPE && R > 0) {
+    {
         if (use_res) {
             u32x2 *bkt = const_cast<u32x2 *>(sBK);
             const uint16_t *bk = p.lora_b + (int64_t)ad * 2 * R * n + (int64_t)h * D;
@@ -283,9 +250,9 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
     f32x4 oacc[8][2];
 #pragma unroll
     for (int mt = 0; mt < 8; ++mt) oacc[mt][0] = oacc[mt][1] = f32x4{0, 0, 0, 0};
-    f32x4 racc[RTX][2];
+    f32x4 racc[RT][2];
 #pragma unroll
-    for (int t = 0; t < RTX; ++t) racc[t][0] = racc[t][1] = f32x4{0, 0, 0, 0};
+    for (int t = 0; t < RT; ++t) racc[t][0] = racc[t][1] = f32x4{0, 0, 0, 0};
     f32x4 lacc[2] = {f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}};  // row sums l
     float m_run[2] = {kNegInf, kNegInf};
     const float cl = p.scale_log2;
@@ -298,8 +265,8 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
         // (last tile, or two buffers: nothing else is in flight)
         if (S::NBUF == 3 && tile + 1 < n_tiles) {
             // per tile a wave copies 4 blocks, plus its rCache page (K waves, with an adapter)
-            // and, RoPE on with an adapter, two table rows
-            constexpr int kTab = (ROPE && R > 0) ? 2 : 0;
+            // and, with an adapter, two table rows
+            constexpr int kTab = 2;
             if (res_copy) wait_vmcnt<4 + RT + kTab>();
             else if (use_res) wait_vmcnt<4 + kTab>();
             else wait_vmcnt<4>();
@@ -321,11 +288,11 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
         // keys of the tile at or past the sequence end (the tile that holds it, or pages
         // past it) may hold any bits in V and C_V: zero them
         const bool ragged = (tile + 1) * TILE_KEYS > L;
-        if constexpr (ROPE && R > 0) {
+        {
             if (use_res) {
                 // Stage 1 for a quarter of page pw: U^T tiles, deferred RoPE, K = K_base +
                 // K_lora in place (keys past the sequence end are masked out of the scores)
-                u32x2 ck[RTX];
+                u32x2 ck[RT];
                 f32x4 u[4];  // u tiles 2 half, 2 half + 1, 2 half + 4, 2 half + 5
 #pragma unroll
                 for (int j = 0; j < 4; ++j) u[j] = f32x4{0, 0, 0, 0};
@@ -335,117 +302,83 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
                 const uint32_t ka = base + S::K_OFF + pw * 4096 + half * 1024;
                 const uint32_t kb = ka + 2 * 1024;
                 u32x4 kf[2];
-                if constexpr (RT == 1) {
-                    // every LDS read of the rebuild under one wait (rCache fragment, B_K^T tiles,
-                    // cos/sin pieces, K fragments): 16 agents x 2048-token chunks, 28.0 -> 26.9 ms
-                    u32x4 c;
-                    u32x2 bkf[4];
-                    asm volatile(
-                        "ds_read_b128 %0, %15\n\t"
-                        "ds_read_b64 %1, %16\n\t"
-                        "ds_read_b64 %2, %16 offset:512\n\t"
-                        "ds_read_b64 %3, %16 offset:2048\n\t"
-                        "ds_read_b64 %4, %16 offset:2560\n\t"
-                        "ds_read_b128 %5, %17\n\t"
-                        "ds_read_b128 %6, %17 offset:64\n\t"
-                        "ds_read_b128 %7, %17 offset:128\n\t"
-                        "ds_read_b128 %8, %17 offset:192\n\t"
-                        "ds_read_b128 %9, %18\n\t"
-                        "ds_read_b128 %10, %18 offset:1024\n\t"
-                        "ds_read_b128 %11, %18 offset:4096\n\t"
-                        "ds_read_b128 %12, %18 offset:5120\n\t"
-                        "ds_read_b128 %13, %19\n\t"
-                        "ds_read_b128 %14, %19 offset:2048\n\t"
-                        "s_waitcnt lgkmcnt(0)"
-                        : "=&v"(c), "=&v"(bkf[0]), "=&v"(bkf[1]), "=&v"(bkf[2]), "=&v"(bkf[3]), "=&v"(rot0[0]), "=&v"(rot0[1]),
-                          "=&v"(rot0[2]), "=&v"(rot0[3]), "=&v"(rotc[0]), "=&v"(rotc[1]), "=&v"(rots[0]), "=&v"(rots[1]),
-                          "=&v"(kf[0]), "=&v"(kf[1])
-                        : "v"(base + S::C_OFF + pw * 1024),
-                          "v"(lds_addr((LdsU32x4 *)lds) + S::MAIN_BYTES + ((2 * half) * 64 + lane) * 8),
-                          "v"(lds_addr(buf(tile)) + S::T_OFF + (pw * 2 + half) * 256 + grp * 16), "v"(colt), "v"(ka)
-                        : "memory");
-                    ck[0] = (4 * grp < R) ? u32x2{c.x, c.y} : u32x2{0, 0};
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) u[j] = mfma16(bkf[j], ck[0], u[j]);
-                } else {
-                    // two groups under one wait each: the rCache fragments and B_K^T tiles of every
-                    // rank tile (rank tile t is 4 KB further in both), then cos/sin and K
-                    u32x4 c[RT];
-                    u32x2 bkf[RT][4];
-                    const uint32_t ca = base + S::C_OFF + pw * 1024;
-                    const uint32_t ba = lds_addr((LdsU32x4 *)lds) + S::MAIN_BYTES + ((2 * half) * 64 + lane) * 8;
-                    static_assert(RT == 2 || RT == 4, "rank tiles");
-                    if constexpr (RT == 2) {
-                        asm volatile(
-                            "ds_read_b128 %0, %10\n\t"
-                            "ds_read_b128 %1, %10 offset:4096\n\t"
-                            "ds_read_b64 %2, %11\n\t"
-                            "ds_read_b64 %3, %11 offset:512\n\t"
-                            "ds_read_b64 %4, %11 offset:2048\n\t"
-                            "ds_read_b64 %5, %11 offset:2560\n\t"
-                            "ds_read_b64 %6, %11 offset:4096\n\t"
-                            "ds_read_b64 %7, %11 offset:4608\n\t"
-                            "ds_read_b64 %8, %11 offset:6144\n\t"
-                            "ds_read_b64 %9, %11 offset:6656\n\t"
-                            "s_waitcnt lgkmcnt(0)"
-                            : "=&v"(c[0]), "=&v"(c[1]), "=&v"(bkf[0][0]), "=&v"(bkf[0][1]), "=&v"(bkf[0][2]),
-                              "=&v"(bkf[0][3]), "=&v"(bkf[1][0]), "=&v"(bkf[1][1]), "=&v"(bkf[1][2]), "=&v"(bkf[1][3])
-                            : "v"(ca), "v"(ba)
-                            : "memory");
-                    } else {
-                        asm volatile(
-                            "ds_read_b128 %0, %20\n\t"
-                            "ds_read_b128 %1, %20 offset:4096\n\t"
-                            "ds_read_b128 %2, %20 offset:8192\n\t"
-                            "ds_read_b128 %3, %20 offset:12288\n\t"
-                            "ds_read_b64 %4, %21\n\t"
-                            "ds_read_b64 %5, %21 offset:512\n\t"
-                            "ds_read_b64 %6, %21 offset:2048\n\t"
-                            "ds_read_b64 %7, %21 offset:2560\n\t"
-                            "ds_read_b64 %8, %21 offset:4096\n\t"
-                            "ds_read_b64 %9, %21 offset:4608\n\t"
-                            "ds_read_b64 %10, %21 offset:6144\n\t"
-                            "ds_read_b64 %11, %21 offset:6656\n\t"
-                            "ds_read_b64 %12, %21 offset:8192\n\t"
-                            "ds_read_b64 %13, %21 offset:8704\n\t"
-                            "ds_read_b64 %14, %21 offset:10240\n\t"
-                            "ds_read_b64 %15, %21 offset:10752\n\t"
-                            "ds_read_b64 %16, %21 offset:12288\n\t"
-                            "ds_read_b64 %17, %21 offset:12800\n\t"
-                            "ds_read_b64 %18, %21 offset:14336\n\t"
-                            "ds_read_b64 %19, %21 offset:14848\n\t"
-                            "s_waitcnt lgkmcnt(0)"
-                            : "=&v"(c[0]), "=&v"(c[1]), "=&v"(c[2]), "=&v"(c[3]), "=&v"(bkf[0][0]), "=&v"(bkf[0][1]),
-                              "=&v"(bkf[0][2]), "=&v"(bkf[0][3]), "=&v"(bkf[1][0]), "=&v"(bkf[1][1]),
-                              "=&v"(bkf[1][2]), "=&v"(bkf[1][3]), "=&v"(bkf[2][0]), "=&v"(bkf[2][1]),
-                              "=&v"(bkf[2][2]), "=&v"(bkf[2][3]), "=&v"(bkf[3][0]), "=&v"(bkf[3][1]),
-                              "=&v"(bkf[3][2]), "=&v"(bkf[3][3])
-                            : "v"(ca), "v"(ba)
-                            : "memory");
-                    }
-#pragma unroll
-                    for (int t = 0; t < RT; ++t) {
-                        ck[t] = (16 * t + 4 * grp < R) ? u32x2{c[t].x, c[t].y} : u32x2{0, 0};
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) u[j] = mfma16(bkf[t][j], ck[t], u[j]);
-                    }
+                // two groups under one wait each: the rCache fragments and B_K^T tiles of every
+                // rank tile (rank tile t is 4 KB further in both), then cos/sin and K
+                u32x4 c[RT];
+                u32x2 bkf[RT][4];
+                const uint32_t ca = base + S::C_OFF + pw * 1024;
+                const uint32_t ba = lds_addr((LdsU32x4 *)lds) + S::MAIN_BYTES + ((2 * half) * 64 + lane) * 8;
+                static_assert(RT == 2 || RT == 4, "rank tiles");
+                if constexpr (RT == 2) {
                     asm volatile(
                         "ds_read_b128 %0, %10\n\t"
-                        "ds_read_b128 %1, %10 offset:64\n\t"
-                        "ds_read_b128 %2, %10 offset:128\n\t"
-                        "ds_read_b128 %3, %10 offset:192\n\t"
-                        "ds_read_b128 %4, %11\n\t"
-                        "ds_read_b128 %5, %11 offset:1024\n\t"
-                        "ds_read_b128 %6, %11 offset:4096\n\t"
-                        "ds_read_b128 %7, %11 offset:5120\n\t"
-                        "ds_read_b128 %8, %12\n\t"
-                        "ds_read_b128 %9, %12 offset:2048\n\t"
+                        "ds_read_b128 %1, %10 offset:4096\n\t"
+                        "ds_read_b64 %2, %11\n\t"
+                        "ds_read_b64 %3, %11 offset:512\n\t"
+                        "ds_read_b64 %4, %11 offset:2048\n\t"
+                        "ds_read_b64 %5, %11 offset:2560\n\t"
+                        "ds_read_b64 %6, %11 offset:4096\n\t"
+                        "ds_read_b64 %7, %11 offset:4608\n\t"
+                        "ds_read_b64 %8, %11 offset:6144\n\t"
+                        "ds_read_b64 %9, %11 offset:6656\n\t"
                         "s_waitcnt lgkmcnt(0)"
-                        : "=&v"(rot0[0]), "=&v"(rot0[1]), "=&v"(rot0[2]), "=&v"(rot0[3]), "=&v"(rotc[0]), "=&v"(rotc[1]),
-                          "=&v"(rots[0]), "=&v"(rots[1]), "=&v"(kf[0]), "=&v"(kf[1])
-                        : "v"(lds_addr(buf(tile)) + S::T_OFF + (pw * 2 + half) * 256 + grp * 16), "v"(colt), "v"(ka)
+                        : "=&v"(c[0]), "=&v"(c[1]), "=&v"(bkf[0][0]), "=&v"(bkf[0][1]), "=&v"(bkf[0][2]),
+                          "=&v"(bkf[0][3]), "=&v"(bkf[1][0]), "=&v"(bkf[1][1]), "=&v"(bkf[1][2]), "=&v"(bkf[1][3])
+                        : "v"(ca), "v"(ba)
+                        : "memory");
+                } else {
+                    asm volatile(
+                        "ds_read_b128 %0, %20\n\t"
+                        "ds_read_b128 %1, %20 offset:4096\n\t"
+                        "ds_read_b128 %2, %20 offset:8192\n\t"
+                        "ds_read_b128 %3, %20 offset:12288\n\t"
+                        "ds_read_b64 %4, %21\n\t"
+                        "ds_read_b64 %5, %21 offset:512\n\t"
+                        "ds_read_b64 %6, %21 offset:2048\n\t"
+                        "ds_read_b64 %7, %21 offset:2560\n\t"
+                        "ds_read_b64 %8, %21 offset:4096\n\t"
+                        "ds_read_b64 %9, %21 offset:4608\n\t"
+                        "ds_read_b64 %10, %21 offset:6144\n\t"
+                        "ds_read_b64 %11, %21 offset:6656\n\t"
+                        "ds_read_b64 %12, %21 offset:8192\n\t"
+                        "ds_read_b64 %13, %21 offset:8704\n\t"
+                        "ds_read_b64 %14, %21 offset:10240\n\t"
+                        "ds_read_b64 %15, %21 offset:10752\n\t"
+                        "ds_read_b64 %16, %21 offset:12288\n\t"
+                        "ds_read_b64 %17, %21 offset:12800\n\t"
+                        "ds_read_b64 %18, %21 offset:14336\n\t"
+                        "ds_read_b64 %19, %21 offset:14848\n\t"
+                        "s_waitcnt lgkmcnt(0)"
+                        : "=&v"(c[0]), "=&v"(c[1]), "=&v"(c[2]), "=&v"(c[3]), "=&v"(bkf[0][0]), "=&v"(bkf[0][1]),
+                          "=&v"(bkf[0][2]), "=&v"(bkf[0][3]), "=&v"(bkf[1][0]), "=&v"(bkf[1][1]),
+                          "=&v"(bkf[1][2]), "=&v"(bkf[1][3]), "=&v"(bkf[2][0]), "=&v"(bkf[2][1]),
+                          "=&v"(bkf[2][2]), "=&v"(bkf[2][3]), "=&v"(bkf[3][0]), "=&v"(bkf[3][1]),
+                          "=&v"(bkf[3][2]), "=&v"(bkf[3][3])
+                        : "v"(ca), "v"(ba)
                         : "memory");
                 }
+#pragma unroll
+                for (int t = 0; t < RT; ++t) {
+                    ck[t] = (16 * t + 4 * grp < R) ? u32x2{c[t].x, c[t].y} : u32x2{0, 0};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) u[j] = mfma16(bkf[t][j], ck[t], u[j]);
+                }
+                asm volatile(
+                    "ds_read_b128 %0, %10\n\t"
+                    "ds_read_b128 %1, %10 offset:64\n\t"
+                    "ds_read_b128 %2, %10 offset:128\n\t"
+                    "ds_read_b128 %3, %10 offset:192\n\t"
+                    "ds_read_b128 %4, %11\n\t"
+                    "ds_read_b128 %5, %11 offset:1024\n\t"
+                    "ds_read_b128 %6, %11 offset:4096\n\t"
+                    "ds_read_b128 %7, %11 offset:5120\n\t"
+                    "ds_read_b128 %8, %12\n\t"
+                    "ds_read_b128 %9, %12 offset:2048\n\t"
+                    "s_waitcnt lgkmcnt(0)"
+                    : "=&v"(rot0[0]), "=&v"(rot0[1]), "=&v"(rot0[2]), "=&v"(rot0[3]), "=&v"(rotc[0]), "=&v"(rotc[1]),
+                      "=&v"(rots[0]), "=&v"(rots[1]), "=&v"(kf[0]), "=&v"(kf[1])
+                    : "v"(lds_addr(buf(tile)) + S::T_OFF + (pw * 2 + half) * 256 + grp * 16), "v"(colt), "v"(ka)
+                    : "memory");
                 // rotate-half pairs (tile m with m + 4) at the key's position p0 + col: the
                 // angle of page start p0 plus the angle of offset col (angle addition)
 #pragma unroll
@@ -498,26 +431,6 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
                 }
             }
         }
-        if constexpr (R > 0 && !ROPE) {
-            if (use_res) {
-#pragma unroll
-                for (int t = 0; t < RT; ++t) {
-                    // rCache fragments of the tile's four pages (C_K in .xy)
-                    u32x4 cf[4];
-                    lds_get4<S::CV>(base + S::C_OFF + t * 4096, cf);
-                    // C_K of rank rows 16t + 4grp .. +3 (rank 8: half a tile is padding)
-                    const bool kvalid = 16 * t + 4 * grp < R;
-#pragma unroll
-                    for (int kt = 0; kt < 4; ++kt) {
-                        const u32x4 ak = u32x4{kvalid ? cf[kt].x : 0u, kvalid ? cf[kt].y : 0u, 0u, 0u};
-                        // zero-padded 16x16x32 form: the chain stays on one instruction form
-                        sacc[kt][0] = mfma32(ak, u32x4{wq[0][t].x, wq[0][t].y, 0u, 0u}, sacc[kt][0]);
-                        sacc[kt][1] = mfma32(ak, u32x4{wq[1][t].x, wq[1][t].y, 0u, 0u}, sacc[kt][1]);
-                    }
-                }
-            }
-        }
-
         // ---- causal mask + online softmax (rows live in lanes) ----
         // A tile below every row's diagonal needs no mask.  The running maximum moves only
         // when some row's scores exceed it by more than 2^kLazyRescale (then acc, acc_r and
@@ -666,7 +579,7 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
     }
 }
 
-template <int R, int G, bool ROPE>
+template <int R, int G>
 hipError_t launch_prefill(const PrefillArgs &pa, hipStream_t st, void *const *ev) {
     hipError_t e;
     const int pairs = (pa.n_agents * pa.hkv + kXcds - 1) / kXcds * kXcds;
@@ -674,14 +587,14 @@ hipError_t launch_prefill(const PrefillArgs &pa, hipStream_t st, void *const *ev
     // timing events carry the kernel's own start and end timestamps (set by the launch)
     hipEvent_t e0 = ev ? static_cast<hipEvent_t>(ev[0]) : nullptr;
     hipEvent_t e1 = ev ? static_cast<hipEvent_t>(ev[1]) : nullptr;
-    hipExtLaunchKernelGGL((prefill_rebuild_kernel<R, G, ROPE>), dim3(grid), dim3(64 * kStreamWaves), 0, st, e0, e1, 0, pa);
+    hipExtLaunchKernelGGL((prefill_rebuild_kernel<R, G>), dim3(grid), dim3(64 * kStreamWaves), 0, st, e0, e1, 0, pa);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return hipSuccess;
 }
 
 template <int G>
 hipError_t dispatch_prefill(int r, const PrefillArgs &pa, hipStream_t st, void *const *ev) {
-    return r == 32 ? launch_prefill<32, G, true>(pa, st, ev) : launch_prefill<64, G, true>(pa, st, ev);
+    return r == 32 ? launch_prefill<32, G>(pa, st, ev) : launch_prefill<64, G>(pa, st, ev);
 }
 
 }  // namespace
