@@ -366,3 +366,17 @@ def test_graph_replay_serves_decode_steps(rope):
             check_close(f"graph step {step} rope={rope}", replayed, oracle_decode(wl, agents, rope))
     other.close()
     lw.close()
+
+
+@pytest.mark.parametrize("hq,r", [(32, 32), (64, 32), (32, 64), (64, 64)])
+@pytest.mark.parametrize("item_agents", [0, 3])
+@pytest.mark.parametrize("root", [0, 200])
+def test_rope_wave_slots_at_high_rank(hq, r, item_agents, root):
+    """With RoPE at ranks 32 and 64 a wave serves two to four agents: full, partly filled and
+    single-agent waves, private contexts of 1 to 21 pages ending on and beside page edges and
+    the same behind a shared prefix; agent 4 has no residual."""
+    suffix = [16, 64, 65, 80, 127, 128, 129, 192, 200, 256, 336, 1, 33]
+    wl = W.explicit(f"wave-slots-hq{hq}-r{r}-{root}", 63, node_parent=[-1], node_len=[root], agent_node=[0] * len(suffix),
+                    suffix=suffix, hq=hq, hkv=8, r=r, b_std=0.05, zero_residual=[4])
+    run_case(f"wave slots hq={hq} r={r} items={item_agents} root={root}", wl, True, residual_delta=False,
+             item_agents=item_agents)
