@@ -361,6 +361,10 @@ int64_t fkv_res_page_elems(int32_t page_size, int32_t r);
  * and res_kv are the pools; hkv, d, r, page_size describe them. */
 fkv_status fkv_page_copy_launch(const fkv_page_copy *copies_dev, int32_t n, void *base_kv, void *res_kv,
                                 int32_t hkv, int32_t d, int32_t r, int32_t page_size, void *stream);
+/* The same for a list in host memory, read before the call returns and passed to the kernel by
+ * value (128 copies per launch): no device copy of the list and no wait for one. */
+fkv_status fkv_page_copy_list(const fkv_page_copy *copies, int32_t n, void *base_kv, void *res_kv, int32_t hkv,
+                              int32_t d, int32_t r, int32_t page_size, void *stream);
 
 /* Write logical rows into the pools through one sequence's block table.
  * Positions pos0 .. pos0+n-1 of the sequence receive

@@ -102,8 +102,7 @@ __device__ __forceinline__ void copy_chunks(const uint16_t *src, uint16_t *dst, 
         if (slot_of(e) < n_valid) dst[e] = src[e];
 }
 
-__global__ __launch_bounds__(256) void page_copy_kernel(CopyArgs a) {
-    const fkv_page_copy c = a.copies[blockIdx.x];
+__device__ __forceinline__ void copy_page(const CopyArgs &a, const fkv_page_copy &c) {
     const int n_valid = c.n_valid;
     const int first = (int)(blockIdx.y * blockDim.x + threadIdx.x), step = (int)(gridDim.y * blockDim.x);
     if (c.pool == FKV_POOL_BASE) {
@@ -141,6 +140,21 @@ __global__ __launch_bounds__(256) void page_copy_kernel(CopyArgs a) {
                 if (c_slot(e, ps, r) < n_valid) dst[e] = src[e];
         }
     }
+}
+
+__global__ __launch_bounds__(256) void page_copy_kernel(CopyArgs a) { copy_page(a, a.copies[blockIdx.x]); }
+
+// The list as a kernel argument: a host list needs no copy to the device, which from pageable memory
+// waits for the work queued before it (eight forks' copies and eight scatter calls: 94 -> 81 us).
+constexpr int kCopyListMax = 128;  // copies per launch (2 KB of kernel arguments)
+struct CopyList {
+    fkv_page_copy c[kCopyListMax];
+};
+__global__ __launch_bounds__(256) void page_copy_list_kernel(CopyArgs a, CopyList l) { copy_page(a, l.c[blockIdx.x]); }
+
+unsigned copy_parts(int32_t hkv, int32_t d, int32_t page_size) {
+    const int64_t chunks = (2LL * hkv * page_size * d + 7) / 8;  // of a base page, the larger of the two as a rule
+    return (unsigned)std::min<int64_t>(kCopyParts, (chunks + 255) / 256);
 }
 
 struct ScatterArgs {
@@ -567,11 +581,29 @@ fkv_status fkv_page_copy_launch(const fkv_page_copy *copies_dev, int32_t n, void
     if (n == 0) return FKV_OK;
     if (!base_kv || (r > 0 && !res_kv)) return fkv::fail(FKV_ERR_INVALID, "fkv_page_copy_launch: pool pointer missing");
     CopyArgs a{copies_dev, static_cast<uint16_t *>(base_kv), static_cast<uint16_t *>(res_kv), hkv, d, r, page_size};
-    const int64_t chunks = (2LL * hkv * page_size * d + 7) / 8;  // of a base page, the larger of the two as a rule
-    const unsigned parts = (unsigned)std::min<int64_t>(kCopyParts, (chunks + 255) / 256);
-    hipLaunchKernelGGL(page_copy_kernel, dim3(n, parts), dim3(256), 0, static_cast<hipStream_t>(stream), a);
+    hipLaunchKernelGGL(page_copy_kernel, dim3(n, copy_parts(hkv, d, page_size)), dim3(256), 0, static_cast<hipStream_t>(stream), a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fkv::fail(FKV_ERR_HIP, std::string("fkv_page_copy_launch: ") + hipGetErrorString(e));
+    return FKV_OK;
+}
+
+fkv_status fkv_page_copy_list(const fkv_page_copy *copies, int32_t n, void *base_kv, void *res_kv, int32_t hkv,
+                              int32_t d, int32_t r, int32_t page_size, void *stream) {
+    fkv::clear_error();
+    if (n < 0 || (n > 0 && !copies) || hkv < 1 || d < 1 || r < 0 || page_size < 1)
+        return fkv::fail(FKV_ERR_INVALID, "fkv_page_copy_list: bad argument");
+    if (n == 0) return FKV_OK;
+    if (!base_kv || (r > 0 && !res_kv)) return fkv::fail(FKV_ERR_INVALID, "fkv_page_copy_list: pool pointer missing");
+    CopyArgs a{nullptr, static_cast<uint16_t *>(base_kv), static_cast<uint16_t *>(res_kv), hkv, d, r, page_size};
+    for (int32_t i = 0; i < n; i += kCopyListMax) {
+        CopyList l{};
+        const int32_t m = std::min(n - i, kCopyListMax);
+        std::copy(copies + i, copies + i + m, l.c);
+        hipLaunchKernelGGL(page_copy_list_kernel, dim3(m, copy_parts(hkv, d, page_size)), dim3(256), 0,
+                           static_cast<hipStream_t>(stream), a, l);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return fkv::fail(FKV_ERR_HIP, std::string("fkv_page_copy_list: ") + hipGetErrorString(e));
+    }
     return FKV_OK;
 }
 

@@ -235,8 +235,15 @@ def rope_tables(d: int, max_pos: int, base: float, device) -> Tuple[torch.Tensor
 
 def page_copy(copies: Sequence[Tuple[int, int, int, int]], base_kv: torch.Tensor, res_kv: Optional[torch.Tensor],
               hkv: int, d: int, r: int, page_size: int, stream=None) -> None:
-    """fkv_page_copy_launch for a list of (pool, src, dst, n_valid)."""
+    """fkv_page_copy_list for a list of (pool, src, dst, n_valid); lists that would take more than
+    four launches go to the device first (fkv_page_copy_launch)."""
     if not copies:
+        return
+    if len(copies) <= 512:
+        host = np.array(copies, dtype=np.int32).reshape(-1, 4)
+        check(N.fkv_page_copy_list(host.ctypes.data, len(copies), base_kv.data_ptr(),
+                                   res_kv.data_ptr() if res_kv is not None else None, hkv, d, r, page_size,
+                                   _stream(stream)), "fkv_page_copy_list")
         return
     arr = torch.tensor(np.array(copies, dtype=np.int32).reshape(-1, 4), device=base_kv.device)
     check(N.fkv_page_copy_launch(arr.data_ptr(), len(copies), base_kv.data_ptr(),
