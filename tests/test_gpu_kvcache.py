@@ -112,3 +112,17 @@ def test_scatter_sources_at_any_alignment(hkv, pos0, n, shift):
     rt.scatter_tokens(None, bt, pos0, None, None, ck, cv, b2, r2, hkv, D, r, PS)
     assert np.array_equal(_host(b1.view(torch.int16)), _host(b2.view(torch.int16)))
     assert np.array_equal(_host(r1.view(torch.int16)), _host(r2.view(torch.int16)))
+
+
+@pytest.mark.parametrize("n", [128, 129, 512, 513])
+def test_page_copy_lists_of_any_length(n):
+    """Lists on both sides of one launch (128 copies) and of the way through device memory (512)."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    base = torch.randn(2 * n, 2, 1, PS * D, generator=g, device="cuda").bfloat16()
+    res = torch.randn(2 * n, 512, generator=g, device="cuda").bfloat16()
+    exp_b, exp_r = base.clone(), res.clone()
+    exp_b[n::2] = base[0:n:2]
+    exp_r[n + 1::2] = res[1:n:2]
+    rt.page_copy([(i % 2, i, n + i, PS) for i in range(n)], base, res, 1, D, 16, PS)
+    assert np.array_equal(_host(base.view(torch.int16)), _host(exp_b.view(torch.int16)))
+    assert np.array_equal(_host(res.view(torch.int16)), _host(exp_r.view(torch.int16)))
