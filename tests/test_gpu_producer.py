@@ -227,3 +227,40 @@ def test_producer_batch_over_32_sequences():
     assert torch.equal(base_batch.view(torch.int16), base_one.view(torch.int16))
     assert torch.equal(res_batch.view(torch.int16), res_one.view(torch.int16))
     assert not torch.equal(base_batch.view(torch.int16), base0.view(torch.int16))
+
+
+@pytest.mark.parametrize("r", [8, 16, 32, 64])
+@pytest.mark.parametrize("hidden", [1024, 3072])
+def test_producer_on_both_sides_of_eight_pages(r, hidden):
+    """Sequences of 1, 8, 9 and 10 pages (eight is the most that sixteen waves take one page at a
+    time) with and without an adapter, in one call: each as a call of its own writes it, and as the
+    oracle does.  Hidden 3072 is six steps per wave, not a multiple of the steps requested together."""
+    hkv, d, ps = 2, 128, 16
+    specs = [(15, 1, True), (7, 120, True), (7, 122, True), (3, 150, True), (9, 5, False), (0, 160, False)]
+    print(f"case producer page counts r={r} hidden={hidden}", flush=True)
+    x, k, v, a, base0, res0, tables, bts = _batch_case(specs, hkv, d, ps, r, hidden, 500 + r, True)
+    xg, kg, vg = _bf16(x), _bf16(k), _bf16(v)
+    ag = [_bf16(ai) for ai in a]
+    seqs, row = [], 0
+    for (p0, n, ad), bt, ai in zip(specs, bts, ag):
+        seqs.append((bt, bt, ai if ad else None, p0, n, row))
+        row += n
+    base_batch, res_batch, base_one, res_one = base0.clone(), res0.clone(), base0.clone(), res0.clone()
+    base_ref, res_ref = base0.clone(), res0.clone()
+    rt.produce_tokens_batch(seqs, xg, kg, vg, tables, base_batch, res_batch, hkv, d, r, ps)
+    segs = []
+    for (bt, btr, ai, p0, n, r0), (_, _, ad), a_np in zip(seqs, specs, a):
+        xs, ks, vs = x[r0:r0 + n], k[r0:r0 + n], v[r0:r0 + n]
+        rt.produce_tokens(bt, btr, p0, xg[r0:r0 + n].contiguous(), kg[r0:r0 + n].contiguous(),
+                          vg[r0:r0 + n].contiguous(), ai, tables, base_one, res_one, hkv, d, r, ps)
+        kr, vr, ckr, cvr = oracle_produce(xs, ks, vs, a_np[0], a_np[1], p0, ROPE_BASE)
+        rt.scatter_tokens(bt, btr, p0, _bf16(kr), _bf16(vr), _bf16(ckr) if ad else None,
+                          _bf16(cvr) if ad else None, base_ref, res_ref, hkv, d, r, ps)
+        if ad:
+            segs.append((bt, p0, n, _shrink_slack(xs, a_np[0]), _shrink_slack(xs, a_np[1])))
+    torch.cuda.synchronize()
+    assert torch.equal(base_batch.view(torch.int16), base_one.view(torch.int16))
+    assert torch.equal(res_batch.view(torch.int16), res_one.view(torch.int16))
+    assert torch.equal(base_batch[:, 1].view(torch.int16), base_ref[:, 1].view(torch.int16)), "V"
+    _within_one_ulp(base_batch[:, 0], base_ref[:, 0], f"K r={r}", _rope_slack(k))
+    _compare_c(res_batch, res_ref, segs, r, f"r={r} hidden={hidden}")
