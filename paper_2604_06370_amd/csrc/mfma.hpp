@@ -57,6 +57,11 @@ __device__ __forceinline__ u32x4 pack8(const f32x16 &x, int i0) {
 }
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+// acc plus both values of a packed bf16 pair (the dot product with ones: one instruction, fp32 accumulation).
+__device__ __forceinline__ float add_bf16_pair(uint32_t w, float acc) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, 0x3f803f80u), acc, false);
+}
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 __device__ __forceinline__ u32x4 ldg128(const void *p) { return *reinterpret_cast<const u32x4 *>(p); }

@@ -576,6 +576,7 @@ __device__ __forceinline__ void prefill_block(const PrefillArgs &p, unsigned cha
             m_run = m_new;
         }
         const float m_use = m_run == kNegInf ? 0.f : m_run;
+        float tsum = 0.f;  // of this tile alone: a sum of 16 pairs keeps its roundings small beside lsum's
         fence();
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
@@ -588,10 +589,12 @@ __device__ __forceinline__ void prefill_block(const PrefillArgs &p, unsigned cha
                 uint32_t pk = pack_bf16(e0, e1);
                 asm volatile("" : "+v"(pk));  // stays here: otherwise the compiler moves the weights past the next barrier
                 pf[w / 4][w % 4] = pk;
-                if constexpr (!LROW) lsum += e0 + e1;
+                // the weights as the value products take them: their rounding cancels in O / l
+                if constexpr (!LROW) tsum = add_bf16_pair(pk, tsum);
             }
             fence();
         }
+        if constexpr (!LROW) lsum += tsum;
         if constexpr (ROPE && !BESIDE) {
             if (wave >= 4) rebuild(t + 2);
         }

@@ -200,3 +200,26 @@ def test_prefill_row_block_sizes(r, rope, n_agents):
     wl = W._build("pf-blocks", 77, 32, 8, 128, r, 16, [-1], [24], [0] * n_agents, suffix, chunk, {1} if r else set(), 0.05)
     lw, g, ref = run_prefill(f"row-blocks r={r} rope={rope} agents={n_agents}", wl, rope)
     lw.close()
+
+
+@pytest.mark.parametrize("r,rope", [(0, False), (8, False), (16, True), (32, False), (32, True), (64, False), (64, True)])
+@pytest.mark.parametrize("n_agents", [3, 17])
+def test_prefill_row_sums_of_peaked_rows(r, rope, n_agents):
+    """Peaked rows (queries of standard deviation 6): the denominator must carry the same bf16
+    rounding of the weights as the value products, or a whole row is off by one factor of up to
+    1 +- 2^-9.  A dim's values differ little over the keys (1 <= |mean| < 2, deviation 0.05), so the
+    weights' rounding itself hardly shows, and the mean relative error of a row's 128 dims is that
+    factor plus the mean of 128 roundings of the output to bf16, each at most 2^-8 of the value and
+    uniform: standard deviation 2^-8 / sqrt(3 * 128) = 2.0e-4 at most.  One agent has no adapter."""
+    rng = np.random.default_rng(3)
+    chunk, suffix = [int(c) for c in rng.integers(20, 64, n_agents)], [int(c) for c in rng.integers(5, 300, n_agents)]
+    wl = W._build("pf-peaked", 91, 32, 8, 128, r, 16, [-1], [300], [0] * n_agents, suffix, chunk, {1} if r else set(),
+                  0.002, q_std=6.0)
+    mean = (1 + rng.random((1, 8, 128))) * rng.choice([-1.0, 1.0], (1, 8, 128))
+    wl.base_v[:] = W.f32_to_bf16_bits(mean + 0.05 * rng.standard_normal(wl.base_v.shape))
+    lw, g, ref = run_prefill(f"peaked r={r} rope={rope} agents={n_agents}", wl, rope)
+    lw.close()
+    factor = ((g - ref) / ref).mean(axis=-1)
+    rms = float(np.sqrt((factor ** 2).mean()))
+    print(f"row factor: rms {rms:.3e} max {np.abs(factor).max():.3e}", flush=True)
+    assert rms <= 2.0 ** -8 / np.sqrt(3 * 128)
