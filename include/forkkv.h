@@ -342,6 +342,12 @@ fkv_status fkv_residual_attention_decode_noalloc(const fkv_attn_args *args, cons
  * keys 0 .. that position.  Same shapes as decode; needs no plan or workspace. */
 fkv_status fkv_residual_attention_prefill(const fkv_attn_args *args, void *stream);
 
+/* The form that call takes for these sizes (max_q: its max_q_per_agent, or n_q): query rows of one
+ * workgroup (128 or 256), and in *pipelined (may be NULL) 1 for prefill_stream_kernel, 0 for
+ * prefill_rebuild_kernel.  Returns 0 for sizes the call does not take. */
+int32_t fkv_prefill_block_rows(int32_t hq, int32_t hkv, int32_t r, int32_t rope, int32_t n_agents, int32_t max_q,
+                               int32_t *pipelined);
+
 /* Fill the RoPE tables on the host (fp64 angles rounded to fp32): for position p
  * and pair i < d/2 the entry is cos(p * base^(-2i/d)) (sin likewise), stored at
  * (p/16)*1024 + (i/16)*256 + (p%16 + 16*((i%16)/4))*4 + i%4, the order in which the

@@ -116,6 +116,8 @@ fkv_residual_attention_decode_noalloc = _sig("fkv_residual_attention_decode_noal
 FKV_NOALLOC_WORKSPACE_BYTES = 64 << 20
 fkv_residual_attention_prefill = _sig("fkv_residual_attention_prefill", c_i32,
                                       [ctypes.POINTER(fkv_attn_args), c_vp])
+fkv_prefill_block_rows = _sig("fkv_prefill_block_rows", c_i32,
+                              [c_i32, c_i32, c_i32, c_i32, c_i32, c_i32, ctypes.POINTER(c_i32)])
 fkv_rope_table = _sig("fkv_rope_table", c_i32, [c_i32, c_i32, c_f64, c_vp, c_vp])
 fkv_res_page_elems = _sig("fkv_res_page_elems", c_i64, [c_i32, c_i32])
 fkv_page_copy_launch = _sig("fkv_page_copy_launch", c_i32, [c_vp, c_i32, c_vp, c_vp, c_i32, c_i32, c_i32, c_i32, c_vp])

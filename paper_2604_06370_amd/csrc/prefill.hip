@@ -597,6 +597,29 @@ hipError_t dispatch_prefill(int r, const PrefillArgs &pa, hipStream_t st, void *
     return r == 32 ? launch_prefill<32, G>(pa, st, ev) : launch_prefill<64, G>(pa, st, ev);
 }
 
+// Which kernel and how many query rows per workgroup:
+//  - RoPE on at rank 64, and at rank 32 unless the grid is small: the rebuild kernel (the
+//    pipelined one spills there: 4 agents x 2048 rows, 8B heads, rank 32: 7.5 ms against 15.5;
+//    rank 64: 7.8 against over 20);
+//  - else the pipelined kernel, with 128 rows per workgroup when 256 would occupy at most half of
+//    the compute units (4 agents x 250 rows over 32K, 8B heads, rank 16, RoPE off: 112 workgroups
+//    920 us, 224 workgroups 844 us, both before the copies went further ahead; now 620) and at
+//    rank 64 (RoPE off), where eight waves spill (4 agents x 2048 rows: 8.4 -> 7.5 ms).
+// An (agent, KV head) pair keeps to one XCD, whose 32 compute units hold one workgroup each, so the
+// grid is small when the XCD with the most pairs is at most half full (one KV head, 12 agents x 600
+// rows over 6000, RoPE on: 40 workgroups of 128 rows on four of the XCDs, two rounds, against 20 of
+// 256: rank 8, 349 and 240 us; rank 32, 393 and, on the rebuild kernel, 344 us).
+struct PrefillForm {
+    bool rebuild;
+    int rows;
+};
+PrefillForm prefill_form(int r, bool rope, int g, int64_t pairs, int64_t max_q) {
+    const int64_t blocks256 = (max_q * g + 255) / 256;
+    const bool few = (pairs + kXcds - 1) / kXcds * blocks256 * 2 <= kCus / kXcds;
+    const bool rebuild = rope && (r == 64 || (r == 32 && !few));
+    return {rebuild, !rebuild && (few || r == 64) ? 128 : 256};
+}
+
 }  // namespace
 
 namespace fkv {
@@ -637,25 +660,23 @@ extern "C" fkv_status fkv_residual_attention_prefill(const fkv_attn_args *a, voi
     const bool rope = a->rope_cos != nullptr && a->r > 0;
     const int maxq = a->max_q_per_agent > 0 ? a->max_q_per_agent : a->n_q;
     if (maxq > a->n_q) return fkv::fail(FKV_ERR_INVALID, "fkv_residual_attention_prefill: max_q_per_agent > n_q");
-    // Which kernel and how many rows per workgroup:
-    //  - RoPE on at rank 64, and at rank 32 unless the grid is small: the rebuild kernel (the
-    //    pipelined one spills there: 4 agents x 2048 rows, 8B heads, rank 32: 7.5 ms against 15.5;
-    //    rank 64: 7.8 against over 20);
-    //  - else the pipelined kernel, with 128 rows per workgroup when 256 would occupy at most half of
-    //    the compute units (4 agents x 250 rows over 32K, 8B heads, rank 16, RoPE off: 112 workgroups
-    //    920 us, 224 workgroups 844 us, both before the copies went further ahead; now 620) and at
-    //    rank 64 (RoPE off), where eight waves spill (4 agents x 2048 rows: 8.4 -> 7.5 ms).
-    const int blocks256 = (int)(((int64_t)maxq * g + 255) / 256);
-    const bool few = (int64_t)a->n_agents * a->hkv * blocks256 <= kCus / 2;
-    const bool rebuild = rope && (a->r == 64 || (a->r == 32 && !few));
-    const bool rows128 = !rebuild && (few || a->r == 64);
-    pa.blocks_per_agent_head = blocks256 * (rows128 ? 2 : 1);
+    const PrefillForm form = prefill_form(a->r, rope, g, (int64_t)a->n_agents * a->hkv, maxq);
+    pa.blocks_per_agent_head = (int)(((int64_t)maxq * g + 255) / 256) * (256 / form.rows);
     pa.scale_log2 = a->scale * 1.4426950408889634f;
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    hipError_t e = !rebuild ? launch_stream(a->r, g, rope, rows128, pa, hs, a->timing_events)
-                   : g == 4 ? dispatch_prefill<4>(a->r, pa, hs, a->timing_events)
-                            : dispatch_prefill<8>(a->r, pa, hs, a->timing_events);
+    hipError_t e = !form.rebuild ? launch_stream(a->r, g, rope, form.rows == 128, pa, hs, a->timing_events)
+                   : g == 4      ? dispatch_prefill<4>(a->r, pa, hs, a->timing_events)
+                                 : dispatch_prefill<8>(a->r, pa, hs, a->timing_events);
     if (e != hipSuccess)
         return fkv::fail(FKV_ERR_HIP, std::string("fkv_residual_attention_prefill: launch failed: ") + hipGetErrorString(e));
     return FKV_OK;
+}
+
+extern "C" int32_t fkv_prefill_block_rows(int32_t hq, int32_t hkv, int32_t r, int32_t rope, int32_t n_agents, int32_t max_q,
+                                          int32_t *pipelined) {
+    const int g = hkv > 0 && hq > 0 && hq % hkv == 0 ? hq / hkv : 0;
+    if ((g != 4 && g != 8) || (r != 0 && r != 8 && r != 16 && r != 32 && r != 64) || n_agents < 1 || max_q < 1) return 0;
+    const PrefillForm form = prefill_form(r, rope != 0 && r > 0, g, (int64_t)n_agents * hkv, max_q);
+    if (pipelined) *pipelined = form.rebuild ? 0 : 1;
+    return form.rows;
 }

@@ -462,3 +462,31 @@ def test_table_validation_names_the_first_bad_entry():
     rt.validate_tables(bb, badr, sl, ad, 16, 5, 10)
     with pytest.raises(rt.FKVError):
         rt.validate_tables(bb, rb, np.array([40, 65], np.int32), ad, 16, 5, 10)   # longer than the rows
+
+
+def test_prefill_form_counts_the_fullest_xcd():
+    """An (agent, KV head) pair keeps to one of the eight XCDs (32 compute units each), so 128 query rows
+    per workgroup are for grids whose fullest XCD stays at most half full with 256: with 12 pairs or 9
+    some XCD has two, with 2 or 3 pairs most have none."""
+    def form(hq, hkv, r, rope, n_agents, max_q):
+        pipelined = ctypes.c_int32(-1)
+        return N.fkv_prefill_block_rows(hq, hkv, r, rope, n_agents, max_q, ctypes.byref(pipelined)), pipelined.value
+
+    # blocks of 256 rows of the fullest XCD: ceil(pairs / 8) * ceil(max_q * g / 256); 16 is half of it
+    for rope in (0, 1):
+        for r in (8, 16):
+            assert form(4, 1, r, rope, 8, 1024) == (128, 1)     # 1 x 16
+            assert form(4, 1, r, rope, 8, 1025) == (256, 1)     # 1 x 17
+            assert form(4, 1, r, rope, 12, 600) == (256, 1)     # 2 x 10 (12 x 10 blocks of 256 in all)
+            assert form(4, 1, r, rope, 12, 512) == (128, 1)     # 2 x 8
+            assert form(4, 1, r, rope, 2, 2000) == (256, 1)     # 1 x 32 on two XCDs
+            assert form(8, 2, r, rope, 5, 600) == (256, 1)      # 10 pairs: 2 x 10
+            assert form(32, 8, r, rope, 4, 250) == (128, 1)     # 4 x 4
+            assert form(64, 8, r, rope, 2, 256) == (128, 1)     # 2 x 8, eight query heads per KV head
+    assert form(4, 1, 32, 1, 12, 600) == (256, 0)               # RoPE at rank 32: the rebuild kernel
+    assert form(4, 1, 32, 1, 12, 512) == (128, 1)
+    assert form(4, 1, 32, 0, 12, 600) == (256, 1)
+    assert form(4, 1, 64, 0, 12, 600) == (128, 1) and form(4, 1, 64, 1, 1, 1) == (256, 0)
+    assert form(32, 8, 0, 1, 4, 250) == (128, 1)                # no residual, nothing to rotate
+    for bad in ((32, 8, 24, 0, 1, 1), (32, 16, 16, 0, 1, 1), (32, 0, 16, 0, 1, 1), (32, 8, 16, 0, 0, 1), (32, 8, 16, 0, 1, 0)):
+        assert form(*bad)[0] == 0
