@@ -626,35 +626,65 @@ __device__ __forceinline__ void prefill_block(const PrefillArgs &p, unsigned cha
     }
     wait_vmcnt<0>();
     lds_fence_barrier();
+    // B_V of the epilogue, four dims per thread and step: requested beside the last values at ranks 32
+    // and 64 (up to rank 16 the loop before has no registers left for it)
+    constexpr int NF = (R * D / 4 + 64 * NW - 1) / (64 * NW), NFX = NF > 0 ? NF : 1;
+    u32x2 bvq[NFX];
+    auto load_bv = [&]() __attribute__((always_inline)) {
+        const uint16_t *bv = p.lora_b + ((int64_t)ad * 2 + 1) * R * n + (int64_t)h * D;
+#pragma unroll
+        for (int k = 0; k < NF; ++k) {
+            const int e = 4 * ((int)threadIdx.x + 64 * NW * k);
+            if (e < R * D) bvq[k] = ldg64(bv + (int64_t)(e / D) * n + e % D);
+        }
+    };
+    if constexpr (R >= 32) load_bv();
     values(std::true_type{}, n_tiles - 1, [](int) {});
     __syncthreads();  // the ring is reused below
 
     // ---- epilogue: O = (acc + acc_r . B_V[h]) / l ----
+    // Bound by LDS: a lane reads the 128 / 2 dims of its half for every rank.  With B_V loaded value by
+    // value, read 8 bytes at a time and the accumulators' rows a multiple of 32 banks apart, short contexts
+    // at ranks 32 and 64 were slower than on the kernel before (12 agents x 600 rows over 300 tokens, 8B
+    // heads, RoPE off: rank 32 218 -> 240 us, now 192; rank 64 320 -> 384, now 289; rank 64 with 16 agents
+    // x 40 rows and eight query heads per KV head, where 128-row workgroups take a second round: 67 -> 101,
+    // now 72).  Ranks two at a time: four took 45 to 70 % longer at rank 64, one 2 %.
     const float l_run = LROW ? __shfl(racc[0][1], r32) : lsum + __shfl_xor(lsum, 32);
     if constexpr (R > 0) {
         float *sBV = reinterpret_cast<float *>(lds);
         float *sAcc = reinterpret_cast<float *>(lds + R * D * 4);
-        const uint16_t *bv = p.lora_b + ((int64_t)ad * 2 + 1) * R * n + (int64_t)h * D;
-        for (int e = threadIdx.x; e < R * D; e += 64 * NW) sBV[e] = bf16_to_f32(bv[(int64_t)(e / D) * n + (e % D)]);
+        if constexpr (R < 32) load_bv();
+        // dim 32i + 16e + 4b + 2hh + j of a rank at 32i + 16e + 8hh + 2b + j: a lane's dims lie side by side
+#pragma unroll
+        for (int k = 0; k < NF; ++k) {
+            const int e = 4 * ((int)threadIdx.x + 64 * NW * k), b = (e / 4) % 4;
+            if (e >= R * D) break;
+            float *at = sBV + (e & ~15) + 2 * b;
+            *reinterpret_cast<f32x2 *>(at) = f32x2{bf16_lo(bvq[k].x), bf16_hi(bvq[k].x)};
+            *reinterpret_cast<f32x2 *>(at + 8) = f32x2{bf16_lo(bvq[k].y), bf16_hi(bvq[k].y)};
+        }
 #pragma unroll
         for (int b = 0; b < NRB; ++b)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int rho = 32 * b + 16 * (i & 1) + 4 * (i / 4) + 2 * hh + (i % 4) / 2;
-                if (rho < R) sAcc[(wave * 32 + r32) * R + rho] = racc[b][i];
+                if (rho < R) sAcc[(wave * 32 + r32) * (R + 1) + rho] = racc[b][i];
             }
         __syncthreads();
+#pragma unroll 2
         for (int rho = 0; rho < R; ++rho) {
-            const float c = sAcc[(wave * 32 + r32) * R + rho];
+            const float c = sAcc[(wave * 32 + r32) * (R + 1) + rho];
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
+                for (int e = 0; e < 2; ++e)
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {  // rows 8b + 4hh + e and + 2: dims 32i + 16e + 4b + 2hh and + 1
-                        const f32x2 v = *reinterpret_cast<const f32x2 *>(sBV + rho * D + 32 * i + 16 * e + 4 * b + 2 * hh);
-                        oacc[i][4 * b + e] += c * v[0];
-                        oacc[i][4 * b + e + 2] += c * v[1];
+                    for (int b2 = 0; b2 < 2; ++b2) {  // rows 8b + 4hh + e and + 2: dims 32i + 16e + 4b + 2hh and + 1
+                        const f32x4 v = *reinterpret_cast<const f32x4 *>(sBV + rho * D + 32 * i + 16 * e + 8 * hh + 4 * b2);
+                        oacc[i][8 * b2 + e] += c * v[0];
+                        oacc[i][8 * b2 + e + 2] += c * v[1];
+                        oacc[i][8 * b2 + 4 + e] += c * v[2];
+                        oacc[i][8 * b2 + 4 + e + 2] += c * v[3];
                     }
         }
     }
@@ -675,7 +705,7 @@ __device__ __forceinline__ void prefill_block(const PrefillArgs &p, unsigned cha
 template <int R, int G, bool ROPE, int NW>
 __global__ __launch_bounds__(64 * NW) void prefill_stream_kernel(PrefillArgs p) {
     constexpr int ROWS = NW * 32, TPW = ROWS / G;
-    constexpr int EPI = R > 0 ? R * D * 4 + ROWS * R * 4 : 0;
+    constexpr int EPI = R > 0 ? R * D * 4 + ROWS * (R + 1) * 4 : 0;
     constexpr int RING = Ring<R, ROPE>::MAIN_BYTES > Ring<0, false>::MAIN_BYTES ? Ring<R, ROPE>::MAIN_BYTES : Ring<0, false>::MAIN_BYTES;
     constexpr int BYTES = RING > EPI ? RING : EPI;
     static_assert(BYTES <= 160 * 1024, "LDS of one workgroup");

@@ -223,3 +223,16 @@ def test_prefill_row_sums_of_peaked_rows(r, rope, n_agents):
     rms = float(np.sqrt((factor ** 2).mean()))
     print(f"row factor: rms {rms:.3e} max {np.abs(factor).max():.3e}", flush=True)
     assert rms <= 2.0 ** -8 / np.sqrt(3 * 128)
+
+
+@pytest.mark.parametrize("r,rope", [(8, False), (8, True), (16, False), (16, True), (32, False), (32, True), (64, False), (64, True)])
+@pytest.mark.parametrize("hq,hkv,n_agents", [(32, 8, 3), (16, 2, 3), (32, 8, 17)])
+def test_prefill_amplified_adapters(r, rope, hq, hkv, n_agents):
+    """C B ~ N(0, 1): the value residual acc_r . B_V that the end of the kernel adds is as large as the
+    base values, on grids of both row-block sizes and with four and eight query heads per KV head.  The
+    context is long enough that no output reaches 4, from where on rounding it to bf16 alone takes 2^-6
+    of the bar's 2e-2."""
+    wl = W.fanout(f"pf-amp-r{r}", 95, n_agents=n_agents, prefix=600, suffix_lo=1, suffix_hi=60, hq=hq, hkv=hkv, r=r,
+                  chunk=45, b_std=1.0 / np.sqrt(r))
+    lw, g, ref = run_prefill(f"prefill amplified r={r} rope={rope} hq={hq} hkv={hkv} agents={n_agents}", wl, rope)
+    lw.close()
