@@ -842,27 +842,30 @@ __global__ __launch_bounds__(256, R >= 64 ? 1 : 2) void decode_split_kernel(Deco
 // other groups from the caches.  The B_K^T fragments of every slot of the item are built in
 // LDS once per workgroup.  Per page and slot s of the wave's group (matrix-core products,
 // fp32 accumulate):
-//   U^T   = B_K,s^T C_K,s^T                  16x16x16; two rank tiles at a time (rank 32, 64): 16x16x32
+//   U^T   = B_K,s^T C_K,s^T                  16x16x16; wide form, two rank tiles at a time: 16x16x32
 // (a 16x16x32 product takes the matrix core as long as a 16x16x16 one: 64 agents over a 128K tree at
 // rank 32, 2339 -> 2243 us; 24 agents with 70B heads at rank 64, bound elsewhere, 361 us either way)
 //   K_lr  = RoPE_p(U)                        rotate-half pairs (i, i + 64) in one lane, fp32
 //   S^T  += K_lr Q^T                         16x16x32, kept for the slot's own rows (columns)
-template <int R, int G>
+template <int R, int G, bool WIDE>
 struct RopeShape {
     static constexpr int RT = (R + 15) / 16;                       // 16-wide rank tiles
-    static constexpr int NSW = fkv::decode_rope_wave_agents(G, R); // agent slots of a wave
+    static constexpr int NSW = fkv::decode_rope_wave_agents(G, R, WIDE);  // agent slots of a wave
     static constexpr int MS = fkv::decode_rope_item_agents(G, R);  // agent slots of an item
-    static constexpr int KT = RT % 2 == 0 ? 2 : 1;                 // rank tiles of one rebuild product
+    // Rank tiles of one rebuild product.  Narrow waves take one: with two, plans of up to 70 us at rank 32
+    // with eight query heads per KV head took up to 7 % longer (8 agents over 4000 tokens 30 -> 32 us)
+    static constexpr int KT = WIDE ? 2 : 1;
     static constexpr int BKT = MS * RT * 8 * 512;                  // (slot, tiles, column tile) x 64 lanes x 8 KT B
     static constexpr int BK_UNITS = MS * RT * 128;                 // (slot, rank pair, 8-dim chunk)
     static_assert(BKT <= 64 * 1024, "two workgroups per compute unit");
-    static_assert(BK_UNITS % 256 == 0 && NSW * G <= ROWS && (KT == 2 || RT == 1), "shape");
+    static_assert(BK_UNITS % 256 == 0 && NSW * G <= ROWS && RT % KT == 0, "shape");
+    static_assert(!WIDE || fkv::decode_rope_has_wide(G, R), "a form of its own");
 };
 
-template <int R, int G>
+template <int R, int G, bool WIDE>
 __global__ __launch_bounds__(256, 2) void decode_rope_kernel(DecodeArgs p) {
     static_assert(R > 0, "RoPE decode needs a residual");
-    using S = RopeShape<R, G>;
+    using S = RopeShape<R, G, WIDE>;
     using RowsT = Rows<R>;
     constexpr int RT = S::RT, NSW = S::NSW, MS = S::MS, KT = S::KT;
     constexpr int RTX = RowsT::RTX;
@@ -1100,7 +1103,9 @@ __global__ __launch_bounds__(256, 2) void decode_rope_kernel(DecodeArgs p) {
                                               u32x4{c0.x, c0.y, c1.x, c1.y}, u[j]);
                             }
                         } else {
-                            u[j] = mfma16(bkt[(slot * 8 + mts[j]) * 64 + lane], cfrag(s, 0, true), u[j]);
+#pragma unroll
+                            for (int t = 0; t < RT; ++t)
+                                u[j] = mfma16(bkt[((slot * RT + t) * 8 + mts[j]) * 64 + lane], cfrag(s, t, true), u[j]);
                         }
                     }
 #pragma unroll
@@ -1274,7 +1279,7 @@ __global__ __launch_bounds__(64 * CW) void decode_combine_kernel(DecodeArgs p) {
 }
 
 template <int R, int G, bool ROPE>
-hipError_t launch_decode(const DecodeArgs &da_in, int n_blocks, int n_agents, bool wide_merge, hipStream_t st,
+hipError_t launch_decode(const DecodeArgs &da_in, int n_blocks, int n_agents, int wave_agents, bool wide_merge, hipStream_t st,
                          void *const *ev) {
     hipError_t e;
     DecodeArgs da = da_in;
@@ -1283,8 +1288,18 @@ hipError_t launch_decode(const DecodeArgs &da_in, int n_blocks, int n_agents, bo
     hipEvent_t e0 = ev ? static_cast<hipEvent_t>(ev[0]) : nullptr;
     hipEvent_t e1 = ev ? static_cast<hipEvent_t>(ev[1]) : nullptr;
     hipEvent_t e2 = ev ? static_cast<hipEvent_t>(ev[2]) : nullptr;
-    if constexpr (ROPE) hipExtLaunchKernelGGL((decode_rope_kernel<R, G>), dim3(n_blocks), dim3(256), 0, st, e0, e1, 0, da);
-    else hipExtLaunchKernelGGL((decode_split_kernel<R, G>), dim3(n_blocks), dim3(256), 0, st, e0, e1, 0, da);
+    if constexpr (ROPE) {
+        if constexpr (fkv::decode_rope_has_wide(G, R)) {
+            if (wave_agents > fkv::decode_rope_wave_agents(G, R, false))
+                hipExtLaunchKernelGGL((decode_rope_kernel<R, G, true>), dim3(n_blocks), dim3(256), 0, st, e0, e1, 0, da);
+            else
+                hipExtLaunchKernelGGL((decode_rope_kernel<R, G, false>), dim3(n_blocks), dim3(256), 0, st, e0, e1, 0, da);
+        } else {
+            hipExtLaunchKernelGGL((decode_rope_kernel<R, G, false>), dim3(n_blocks), dim3(256), 0, st, e0, e1, 0, da);
+        }
+    } else {
+        hipExtLaunchKernelGGL((decode_split_kernel<R, G>), dim3(n_blocks), dim3(256), 0, st, e0, e1, 0, da);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (!wide_merge)
         hipExtLaunchKernelGGL((decode_combine_kernel<R, G, kCombineWaves>), dim3(da.n_rows), dim3(64 * kCombineWaves), 0, st,
@@ -1297,24 +1312,25 @@ hipError_t launch_decode(const DecodeArgs &da_in, int n_blocks, int n_agents, bo
 }
 
 template <int R, int G>
-hipError_t dispatch_rope(bool rope, const DecodeArgs &da, int nb, int na, bool wide, hipStream_t st, void *const *ev) {
+hipError_t dispatch_rope(bool rope, const DecodeArgs &da, int nb, int na, int wa, bool wide, hipStream_t st,
+                         void *const *ev) {
     if constexpr (R == 0) {
-        return launch_decode<0, G, false>(da, nb, na, wide, st, ev);
+        return launch_decode<0, G, false>(da, nb, na, wa, wide, st, ev);
     } else {
-        return rope ? launch_decode<R, G, true>(da, nb, na, wide, st, ev)
-                    : launch_decode<R, G, false>(da, nb, na, wide, st, ev);
+        return rope ? launch_decode<R, G, true>(da, nb, na, wa, wide, st, ev)
+                    : launch_decode<R, G, false>(da, nb, na, wa, wide, st, ev);
     }
 }
 
 template <int G>
-hipError_t dispatch_rank(int r, bool rope, const DecodeArgs &da, int nb, int na, bool wide, hipStream_t st,
+hipError_t dispatch_rank(int r, bool rope, const DecodeArgs &da, int nb, int na, int wa, bool wide, hipStream_t st,
                          void *const *ev) {
     switch (r) {
-    case 0: return dispatch_rope<0, G>(rope, da, nb, na, wide, st, ev);
-    case 8: return dispatch_rope<8, G>(rope, da, nb, na, wide, st, ev);
-    case 16: return dispatch_rope<16, G>(rope, da, nb, na, wide, st, ev);
-    case 32: return dispatch_rope<32, G>(rope, da, nb, na, wide, st, ev);
-    case 64: return dispatch_rope<64, G>(rope, da, nb, na, wide, st, ev);
+    case 0: return dispatch_rope<0, G>(rope, da, nb, na, wa, wide, st, ev);
+    case 8: return dispatch_rope<8, G>(rope, da, nb, na, wa, wide, st, ev);
+    case 16: return dispatch_rope<16, G>(rope, da, nb, na, wa, wide, st, ev);
+    case 32: return dispatch_rope<32, G>(rope, da, nb, na, wa, wide, st, ev);
+    case 64: return dispatch_rope<64, G>(rope, da, nb, na, wa, wide, st, ev);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1401,8 +1417,9 @@ fkv_status decode_impl(const fkv_attn_args *a, const fkv_plan *plan, void *strea
     // and each row has many partials (at least 128 on average); four otherwise.
     const int64_t total_partials = w[w[fkv::H_OFF_AGENT_PTR] + a->n_agents];
     const bool wide = (int64_t)a->n_agents * a->hq < kCus / 2 && total_partials >= 128LL * a->n_agents;
-    hipError_t e = g == 4 ? dispatch_rank<4>(a->r, rope, da, nb, a->n_agents, wide, hs, a->timing_events)
-                          : dispatch_rank<8>(a->r, rope, da, nb, a->n_agents, wide, hs, a->timing_events);
+    const int wa = w[fkv::H_AGENTS_PER_ITEM];  // agents per wave that the plan was laid out for
+    hipError_t e = g == 4 ? dispatch_rank<4>(a->r, rope, da, nb, a->n_agents, wa, wide, hs, a->timing_events)
+                          : dispatch_rank<8>(a->r, rope, da, nb, a->n_agents, wa, wide, hs, a->timing_events);
     if (e != hipSuccess)
         return fkv::fail(FKV_ERR_HIP, std::string("fkv_residual_attention_decode: launch failed: ") + hipGetErrorString(e));
     return FKV_OK;

@@ -74,22 +74,27 @@ constexpr int decode_wave_slots(int g, int r) {
     return r >= 64 ? (kMaxRows / g < 2 ? kMaxRows / g : 2) : kMaxRows / g;
 }
 constexpr int decode_heads_per_block(int, bool) { return 1; }
-// With RoPE a wave serves NSW agents: all the agents of a 16-row group up to rank 32, two at rank 64
-// (as many as keep the rCache fragments of a page in registers without scratch).  A wave pays its
-// page's K, V and RoPE rows, base scores, softmax and value products once for all of them: with
-// four slots instead of two at rank 32, 64 agents over a 128K tree 2243 -> 1929 us; with two
-// instead of one at rank 64, 24 agents with 70B heads 361 -> 305 us.
+// With RoPE a wave serves NSW agents: all the agents of a 16-row group below rank 32, two at rank 32
+// and one at rank 64; or, in the kernel's wide form, all of the group at rank 32 and two at rank 64
+// (as many as keep the rCache fragments of a page in registers without scratch).  A wide wave pays
+// its page's K, V and RoPE rows, base scores, softmax and value products once for twice the agents,
+// but starts up later and does more per page for slots that an item does not fill; rope_wide_pays
+// in plan.cpp says which plans take it.
 // An item holds up to four such wave groups, as many slots as 64 KB of B_K^T fragments
-// (kept in LDS for the launch) allow.
-constexpr int decode_rope_wave_agents(int g, int r) {
-    const int ag = kMaxRows / g;
-    return r >= 64 ? (ag < 2 ? ag : 2) : ag;
+// (kept in LDS for the launch) allow: the same number in both forms.
+constexpr int decode_rope_wave_agents(int g, int r, bool wide) {
+    const int ag = kMaxRows / g, n = r >= 64 ? (wide ? 2 : 1) : (r >= 32 && !wide ? 2 : ag);
+    return ag < n ? ag : n;
+}
+constexpr bool decode_rope_has_wide(int g, int r) {
+    return decode_rope_wave_agents(g, r, true) > decode_rope_wave_agents(g, r, false);
 }
 constexpr int decode_rope_item_agents(int g, int r) {
     const int rt = r <= 16 ? 1 : (r + 15) / 16;
-    const int ms = 4 * decode_rope_wave_agents(g, r);
+    const int ms = 4 * decode_rope_wave_agents(g, r, false);
     return ms < 16 / rt ? ms : 16 / rt;
 }
+static_assert(decode_rope_item_agents(4, 32) == 8 && decode_rope_item_agents(8, 64) == 4, "both forms' items: 16 / rank tiles");
 // Agent groups one RoPE-off work item may hold: four below rank 32; two at rank 32 and at
 // rank 64 when one wave serves a whole group (a stage's rCache fragments of a group then fit the
 // registers of four groups at rank 16); one otherwise.

@@ -27,6 +27,18 @@ constexpr int kNumXcd = 8;
 // prologue, used to size and order the work items.
 double item_page_cost(int32_t agents) { return 1.0 + 0.095 * (double)agents; }
 constexpr double kItemOverhead = 24.0;
+// Decode with RoPE at ranks 32 and 64: whether a plan takes waves of twice the agents
+// (decode_rope_wave_agents).  `all` counts the pages that narrow waves walk, over items and KV heads,
+// `saved` those that wide waves would not.  Measured over 590 plans (one and eight KV heads, four and
+// eight query heads each, 1 to 64 agents, 500 to 131072 shared tokens), times of the wide form in
+// those of the narrow one by the pages saved per compute unit: below 48, 0.88 to 1.27 (6 agents over
+// 500 tokens at rank 32, 13.5 -> 17.2 us; 12 over 40000 at one KV head 1.16); 48 to 64, 0.89 to 1.05; 64
+// to 130, 0.86 to 1.01; 400 and more, 0.73 to 0.86 (64 agents over a 128K tree at rank 32, 2243 -> 1929 us;
+// 24 with 70B heads at rank 64, 361 -> 305).  An item of one agent has nothing to save and takes up to
+// 4 % longer (24 agents of 1000 to 8000 tokens alone, rank 64: 117 -> 122 us), so at least an eighth of
+// the pages has to go.
+constexpr int64_t kWideSavedPages = 48;
+bool rope_wide_pays(int64_t all, int64_t saved, int64_t cus) { return saved >= kWideSavedPages * cus && 8 * saved >= all; }
 }
 
 extern "C" {
@@ -46,8 +58,6 @@ fkv_status fkv_decode_plan_create(const fkv_decode_plan_params *prm, const int32
     if (g > fkv::kMaxRows) return fkv::fail(FKV_ERR_UNSUPPORTED, "fkv_decode_plan_create: more than 16 query heads per KV head");
     if (prm->r < 0 || prm->max_item_agents < 0) return fkv::fail(FKV_ERR_INVALID, "fkv_decode_plan_create: bad r / max_item_agents");
     const bool rope = prm->rope != 0 && prm->r > 0;
-    // agents per group: the slots one wave serves (RoPE) or that fill a 16-row tile
-    const int32_t ag = rope ? fkv::decode_rope_wave_agents(g, prm->r) : fkv::kMaxRows / g;
     const int32_t hpb = fkv::decode_heads_per_block(prm->hkv, rope);
     const int32_t cap = fkv::decode_item_agent_cap(g, prm->hkv, prm->r, rope);
     if (cap < 1) return fkv::fail(FKV_ERR_UNSUPPORTED, "fkv_decode_plan_create: rank too large for the decode kernels");
@@ -90,6 +100,22 @@ fkv_status fkv_decode_plan_create(const fkv_decode_plan_params *prm, const int32
                 for (int32_t a : gr) open[a] = (int32_t)segs.size() - 1;
             }
         }
+    }
+
+    // agents per group: the slots one wave serves (RoPE) or that fill a 16-row tile
+    int32_t ag = fkv::kMaxRows / g;
+    if (rope) {
+        const int32_t narrow = fkv::decode_rope_wave_agents(g, prm->r, false), wide = fkv::decode_rope_wave_agents(g, prm->r, true);
+        int64_t all = 0, saved = 0;  // page visits of a wave in the narrow form, and those that wide waves save
+        for (const Seg &s : segs)
+            for (int32_t k = 0; k < (int32_t)s.agents.size(); k += item_agents) {
+                const int32_t c = std::min<int32_t>(item_agents, (int32_t)s.agents.size() - k);
+                const int64_t n = (c + narrow - 1) / narrow;
+                all += s.n * n;
+                saved += s.n * (n - (c + wide - 1) / wide);
+            }
+        const int64_t cus = prm->num_cus > 0 ? prm->num_cus : 256;
+        ag = rope_wide_pays(all * prm->hkv, saved * prm->hkv, cus) ? wide : narrow;
     }
 
     // 2. agent chunks per segment: up to item_agents agents, in whole groups of ag where

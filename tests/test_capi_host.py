@@ -490,3 +490,36 @@ def test_prefill_form_counts_the_fullest_xcd():
     assert form(32, 8, 0, 1, 4, 250) == (128, 1)                # no residual, nothing to rotate
     for bad in ((32, 8, 24, 0, 1, 1), (32, 16, 16, 0, 1, 1), (32, 0, 16, 0, 1, 1), (32, 8, 16, 0, 0, 1), (32, 8, 16, 0, 1, 0)):
         assert form(*bad)[0] == 0
+
+
+@pytest.mark.parametrize("hq,hkv,r,narrow,wide", [(32, 8, 32, 2, 4), (4, 1, 32, 2, 4), (32, 8, 64, 1, 2), (64, 8, 64, 1, 2),
+                                                  (64, 8, 32, 2, 2), (32, 8, 16, 4, 4), (64, 8, 8, 2, 2)])
+def test_decode_plan_takes_wide_waves_where_they_save_enough(hq, hkv, r, narrow, wide):
+    """RoPE on at ranks 32 and 64: waves of twice the agents where 48 or more page visits per compute
+    unit go, none for small or private contexts.  Narrow plans are those that the page rules were
+    measured on: three wave groups are split 2 + 1, items of more than one group spread over every
+    compute unit."""
+    agents = 16
+    groups = min(agents, rt.decode_plan_default_agents(hq, hkv, r, True)) // narrow  # per full item
+    per_page = hkv * (agents // (groups * narrow)) * (groups - groups * narrow // wide)  # visits saved per shared page
+    edge = -(-48 * 256 // per_page) if per_page else 5000
+
+    def plan(n, shared, private, **kw):
+        bb, sl = _fanout_tables(n, shared, [private] * n)
+        p = rt.DecodePlan(bb, sl, hq, hkv, 16, r=r, rope=True, **kw)
+        words = p.serialize()
+        p.close()
+        return int(words[6]), _parse_plan(words)[1]
+
+    assert plan(agents, edge, 4)[0] == wide
+    assert plan(agents, edge - 1, 4)[0] == narrow
+    assert plan(agents, edge, 4, max_item_agents=narrow)[0] == narrow  # nothing to save
+    assert plan(agents, edge, 8 * edge)[0] == narrow                     # private pages: the most of it
+    assert plan(agents, 64 if per_page else 5000, 0, num_cus=1)[0] == wide
+    if narrow < wide:
+        n = 3 * narrow  # three narrow groups over a 512-token root
+        wa, items = plan(n, 32, 4)
+        assert wa == narrow and {it["nag"] for it in items if it["p0"] < 32} == {2 * narrow, narrow}
+        # two narrow groups (one wide one) over 4096 tokens: spread over the compute units
+        _, items = plan(2 * narrow, 256, 4)
+        assert max(it["end"] - it["p0"] for it in items if it["nag"] == 2 * narrow) <= 8

@@ -14,6 +14,7 @@ import pytest
 import torch
 
 import oracle
+from paper_2604_06370_amd import runtime as rt
 from paper_2604_06370_amd import workloads as W
 from paper_2604_06370_amd.driver import LoadedWorkload
 
@@ -380,3 +381,26 @@ def test_rope_wave_slots_at_high_rank(hq, r, item_agents, root):
                     suffix=suffix, hq=hq, hkv=8, r=r, b_std=0.05, zero_residual=[4])
     run_case(f"wave slots hq={hq} r={r} items={item_agents} root={root}", wl, True, residual_delta=False,
              item_agents=item_agents)
+
+
+def _wide_waves(monkeypatch):
+    """Plans for one compute unit: the page visits that wide waves save then always count as enough."""
+    real = rt.DecodePlan
+    monkeypatch.setattr(rt, "DecodePlan", lambda *a, **k: real(*a, **{**k, "num_cus": 1}))
+
+
+@pytest.mark.parametrize("hq,r", [(32, 32), (32, 64), (64, 64)])
+@pytest.mark.parametrize("item_agents", [0, 3])
+@pytest.mark.parametrize("pps", [0, 5])
+def test_rope_wide_waves(monkeypatch, hq, r, item_agents, pps):
+    """The form whose waves serve two (rank 64) or four agents (rank 32), which plans of this size
+    do not take by themselves: full, partly filled and single-agent waves, long and short items."""
+    _wide_waves(monkeypatch)
+    suffix = [16, 64, 65, 80, 127, 128, 129, 192, 200, 256, 336, 1, 33]
+    wl = W.explicit(f"wide-waves-hq{hq}-r{r}", 64, node_parent=[-1], node_len=[1100], agent_node=[0] * len(suffix),
+                    suffix=suffix, hq=hq, hkv=8, r=r, b_std=0.05, zero_residual=[4])
+    lw = LoadedWorkload(wl, rope=True)
+    assert int(lw.decode_setup()["plan"].serialize()[6]) == (4 if r == 32 else 2)
+    lw.close()
+    run_case(f"wide waves hq={hq} r={r} items={item_agents} pages={pps}", wl, True, residual_delta=False,
+             item_agents=item_agents, pages_per_split=pps)
