@@ -135,7 +135,7 @@ struct Rows {
 // partial is exact whichever m it ends with.
 constexpr float kLazyRescale = 8.f;
 
-template <int R, int NS, bool LEN_MASK = true>
+template <int R, int NS, bool LEN_MASK = true, bool OWN = false>
 __device__ __forceinline__ void softmax_pv(Rows<R> &st, f32x4 sacc, bool valid, int tok0, int len, float scale_log2,
                                            const u32x2 *vf, const u32x2 (*cv)[Rows<R>::RTX], int my_slot_l,
                                            int grp) {
@@ -172,10 +172,22 @@ __device__ __forceinline__ void softmax_pv(Rows<R> &st, f32x4 sacc, bool valid, 
     for (int mt = 0; mt < 8; ++mt) st.oacc[mt] = mfma16(vf[mt], pf, st.oacc[mt]);
     if constexpr (R > 0) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
+        for (int s = 0; s < (OWN ? 0 : NS); ++s) {
             const u32x2 pm = my_slot_l == s ? pf : u32x2{0, 0};
 #pragma unroll
             for (int t = 0; t < Rows<R>::RT; ++t) st.racc[t] = mfma16(cv[s][t], pm, st.racc[t]);
+        }
+        // OWN: two chains from the same old value, of the lower and the upper half of the slots, of which a row
+        // keeps its own: a zero weight times a NaN or infinity of the other half's agents would reach it.
+        // As far apart as in the narrow form: one agent at rank 64, two at rank 32 (where a chain per agent
+        // cost 0.8 % over 64 agents and a 128K tree)
+#pragma unroll
+        for (int t = 0; t < (OWN ? Rows<R>::RT : 0); ++t) {
+            f32x4 x[2] = {st.racc[t], st.racc[t]};
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                x[2 * s / NS] = mfma16(cv[s][t], NS == 2 || my_slot_l == s ? pf : u32x2{0, 0}, x[2 * s / NS]);
+            st.racc[t] = my_slot_l < NS / 2 ? x[0] : x[1];
         }
     }
 }
@@ -1149,7 +1161,7 @@ __global__ __launch_bounds__(256, 2) void decode_rope_kernel(DecodeArgs p) {
                 for (int mt = 0; mt < 8; ++mt) vf[mt] = mask4(vf[mt], vis, grp);
             }
         }
-        softmax_pv<R, NSW, EDGE>(st, sacc, row_active, tok0, my_len, p.scale_log2, vf, cv, my_slot, grp);
+        softmax_pv<R, NSW, EDGE, WIDE>(st, sacc, row_active, tok0, my_len, p.scale_log2, vf, cv, my_slot, grp);
         load_v(next);
     };
     // interior pages first (a prefix of the wave's pages), then the rest

@@ -404,3 +404,25 @@ def test_rope_wide_waves(monkeypatch, hq, r, item_agents, pps):
     lw.close()
     run_case(f"wide waves hq={hq} r={r} items={item_agents} pages={pps}", wl, True, residual_delta=False,
              item_agents=item_agents, pages_per_split=pps)
+
+
+@pytest.mark.parametrize("hq,r,wide", [(32, 32, True), (32, 32, False), (32, 64, True), (64, 64, True), (32, 64, False),
+                                       (64, 64, False)])
+def test_rope_agents_of_a_wave_are_isolated(monkeypatch, hq, r, wide):
+    """NaN in the rCache pages of agent 1 stays in agent 1's rows at rank 64 and does not leave the pair
+    (agents 0 and 1) at rank 32, also in waves of twice the agents: 0 x NaN is NaN."""
+    if wide:
+        _wide_waves(monkeypatch)
+    wl = W.explicit(f"isolated-hq{hq}-r{r}", 65, node_parent=[-1], node_len=[700], agent_node=[0] * 4,
+                    suffix=[40, 50, 3, 90], hq=hq, hkv=8, r=r, b_std=0.05)
+    lw = LoadedWorkload(wl, rope=True)
+    st = lw.decode_setup()
+    pages = st["host_bt"][1][1][:(int(wl.seq_len[1]) + 15) // 16]
+    lw.res_kv[torch.from_numpy(pages).long().cuda()] = float("nan")
+    out = lw.decode().float().cpu().numpy()
+    ref = oracle_decode(wl, wl.decode_agents(), True)
+    others = [2, 3] if r == 32 else [0, 2, 3]
+    assert np.isnan(out[1]).any() and np.isfinite(out[others]).all()
+    err = np.abs(out[others] - ref[others])
+    assert err.max() <= TOL_MAX and err.mean() <= TOL_MEAN
+    lw.close()
