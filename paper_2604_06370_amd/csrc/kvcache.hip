@@ -309,7 +309,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(ScatterArgs a) {
 // head dim 128 (the fragment layouts).  Every workgroup covers one page of the call's
 // position range (slots outside [pos0, pos0 + n) are left as they are).  One launch, two
 // kinds of workgroups:
-//  - shrink (one per four pages): wave w covers every fourth block of the hidden dimension with 16x16x32
+//  - shrink (one per four pages, or one per page, see one_page_shrink): wave w covers every fourth block of the hidden dimension with 16x16x32
 //    products (16 bytes of one token's x row and of one row of A per lane, A L2-resident),
 //    eight k-steps of loads in flight; the four partial tiles are summed through LDS.  C_K is
 //    computed transposed (A as the row operand), so each lane holds 4 ranks of one token
@@ -336,24 +336,15 @@ struct ProduceArgs {
 };
 constexpr int kProdChunk = 1024;  // hidden is a multiple of this (four waves x 8 k-steps x 32)
 constexpr int kProdHeads = 2;     // KV heads per base workgroup
-constexpr int kShrinkPages = 4;   // pages (16-token tiles) per shrink workgroup
-// Sequences of at most kWidePages pages take produce_wide_kernel (a full launch of 32 of them is then
-// one page per compute unit), but not those of few tokens, for which the four waves of
-// produce_kernel read little: 4 sequences at hidden 4096, four waves against sixteen: 64 tokens,
-// rank 16: 24.4 / 17.6 us (rank 8: 21.8 / 13.7, rank 64: 47.0 / 37.8); 9 tokens: 12.0 / 15.7 (rank
-// 32: 21.6 / 22.1, rank 64: 34.2 / 36.0); 1 token (12 sequences): 11.3 / 14.4 (rank 32: 23.2 / 21.1,
-// rank 64: 39.7 / 35.2).  The rule looks at one sequence alone, so what is written for it does not
-// depend on the sequences beside it.
-constexpr int kWidePages = 8;
-constexpr bool wide_shrink(int64_t pages, int64_t n, int r) { return pages <= kWidePages && (n > 16 || (r >= 32 && n <= 4)); }
-
-// The sequence that workgroup `bid` serves: the last one whose first workgroup of this kind is at or below it.
-__device__ __forceinline__ int produce_seq(const ProduceArgs &a, bool shrink_wg, int bid) {
-    int s = 0;
-    for (int j = 1; j < a.nseq; ++j)
-        if ((shrink_wg ? a.seq[j].first_shrink : a.seq[j].first_base) <= bid) s = j;
-    return s;
-}
+constexpr int kShrinkPages = 4;   // pages (16-token tiles) per shrink workgroup of long sequences
+// One page per shrink workgroup where no sequence of the call has more than eight (decode steps, short
+// chunks): such a call is a chain of memory latencies, and one page's registers hold four times the steps
+// in flight (4 sequences at hidden 4096, four pages and one: 64 tokens, rank 16, 25.9 / 13.5 us; rank 64,
+// 48.1 / 34.7; 9 tokens, rank 32, 23.4 / 19.1; one token as many us or up to a quarter fewer).  Longer sequences
+// decide for the call, as they set its time (16 of 1 to 2000 tokens: up to 13 % longer with one page for
+// the short ones among them).  At rank 64 a workgroup takes half of a compute unit, so that a full launch of
+// one-page ones comes in more rounds (32 sequences of 112 tokens, 56.1 / 59.6 us; of 64 tokens 55.5 / 43.3).
+constexpr bool one_page_shrink(int64_t longest, int64_t total, int r) { return longest <= 8 && (r < 64 || total <= 192); }
 
 // Tile t of a page's shrink results (C_K^T below RT, then C_V) into the residual page `pg`; slot 0 of
 // the page is call index tj0 of nq.
@@ -380,113 +371,9 @@ __device__ __forceinline__ void store_shrink(const fkvk::f32x4 &c, int t, uint16
     }
 }
 
-// Base workgroup lb of sequence q on 256 threads, for produce_wide_kernel.  produce_kernel has the same
-// steps in its own body: called as this function there, 16 chunks of 2048 tokens took 134.4 instead of
-// 129.7 us.
-__device__ __forceinline__ void produce_base(const ProduceArgs &a, const ProduceSeq &q, int lb, int64_t pos0, int64_t nq, int64_t page0) {
-    constexpr int PS = 16, D = 128, HALF = D / 2;
-    // base K (rotated) and V of one page and up to kProdHeads KV heads: every head's token
-    // rows are requested before the first one is stored into LDS
-    __shared__ __attribute__((aligned(16))) uint16_t s_k[kProdHeads][PS * D], s_v[kProdHeads][PS * D];  // [slot][dim]
-    const int n_hg = (a.hkv + kProdHeads - 1) / kProdHeads;
-    const int b = lb;
-    const int h0 = (b % n_hg) * kProdHeads;
-    const int nh = min(kProdHeads, a.hkv - h0);
-    const int64_t pp = page0 + b / n_hg;
-    const int64_t tj0 = pp * PS - pos0;  // call index of slot 0 (negative on a first partial page)
-    {
-        const int t = threadIdx.x >> 4, c = threadIdx.x & 15;
-        const int64_t tj = tj0 + t;
-        const bool ok = tj >= 0 && tj < nq;
-        fkvk::u32x4 kx[kProdHeads], vx[kProdHeads];
-#pragma unroll
-        for (int i = 0; i < kProdHeads; ++i) {
-            kx[i] = vx[i] = fkvk::u32x4{0, 0, 0, 0};
-            if (ok && i < nh) {
-                const int64_t src = ((q.row0 + tj) * a.hkv + h0 + i) * D + 8 * c;
-                kx[i] = fkvk::ldg128(a.k_raw + src);
-                vx[i] = fkvk::ldg128(a.v + src);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kProdHeads; ++i) {
-            *reinterpret_cast<fkvk::u32x4 *>(&s_k[i][t * D + 8 * c]) = kx[i];
-            *reinterpret_cast<fkvk::u32x4 *>(&s_v[i][t * D + 8 * c]) = vx[i];
-        }
-    }
-    __syncthreads();
-    constexpr int64_t blk = PS * D;
-    uint16_t *const pg = a.base_kv + (int64_t)q.bt_base[pp] * 2 * a.hkv * blk;
-    if (threadIdx.x < 128) {
-        // K chunks (a2, t, b4) and (a2 + 2, t, b4): element 4h + i is dim f = 32 a2 + 16 h + 4 b4 + i
-        // (the first member of a rotate-half pair) and f + 64 (its partner)
-        const int t = threadIdx.x & 15, b4 = (threadIdx.x >> 4) & 3, a2 = threadIdx.x >> 6;
-        const int64_t tj = tj0 + t;
-        if (tj < 0 || tj >= nq) return;
-        fkvk::f32x4 cs[2], sn[2];
-        if (a.rope_cos) {
-            // table order [pos / 16][f / 16][pos % 16 + 16 ((f % 16) / 4)][f % 4]
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int64_t o = pp * (PS * HALF) + (2 * a2 + h) * 256 + (t + 16 * b4) * 4;
-                cs[h] = *reinterpret_cast<const fkvk::f32x4 *>(a.rope_cos + o);
-                sn[h] = *reinterpret_cast<const fkvk::f32x4 *>(a.rope_sin + o);
-            }
-        }
-        for (int hi = 0; hi < nh; ++hi) {
-            float x0[8], x1[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int f = 32 * a2 + 16 * (e >> 2) + 4 * b4 + (e & 3);
-                x0[e] = fkvk::bf16_to_f32(s_k[hi][t * D + f]);
-                x1[e] = fkvk::bf16_to_f32(s_k[hi][t * D + f + HALF]);
-            }
-            if (a.rope_cos) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float c = cs[e >> 2][e & 3], s = sn[e >> 2][e & 3];
-                    const float u = x0[e], w = x1[e];
-                    x0[e] = u * c - w * s;
-                    x1[e] = w * c + u * s;
-                }
-            }
-            uint16_t *kb = pg + (h0 + hi) * blk + (t + 16 * b4) * 8;
-            *reinterpret_cast<fkvk::u32x4 *>(kb + a2 * 512) =
-                fkvk::u32x4{fkvk::pack_bf16(x0[0], x0[1]), fkvk::pack_bf16(x0[2], x0[3]), fkvk::pack_bf16(x0[4], x0[5]),
-                            fkvk::pack_bf16(x0[6], x0[7])};
-            *reinterpret_cast<fkvk::u32x4 *>(kb + (a2 + 2) * 512) =
-                fkvk::u32x4{fkvk::pack_bf16(x1[0], x1[1]), fkvk::pack_bf16(x1[2], x1[3]), fkvk::pack_bf16(x1[4], x1[5]),
-                            fkvk::pack_bf16(x1[6], x1[7])};
-        }
-    } else {
-        // V chunks ci and ci + 128 (ci = 64 a + 16 q + c): element 4h + i is (dim 32a + 16h + c, token 4q + i)
-        for (int hi = 0; hi < nh; ++hi) {
-            uint16_t *vb = pg + (a.hkv + h0 + hi) * blk;
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const int ci = (int)threadIdx.x - 128 + 128 * half;
-                const int av = ci >> 6, q = (ci >> 4) & 3, c = ci & 15;
-                uint16_t e8[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) e8[e] = s_v[hi][(4 * q + (e & 3)) * D + 32 * av + 16 * (e >> 2) + c];
-                const int64_t tf = tj0 + 4 * q;
-                if (tf >= 0 && tf + 3 < nq) {
-                    fkvk::u32x4 w;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) w[j] = (uint32_t)e8[2 * j] | ((uint32_t)e8[2 * j + 1] << 16);
-                    *reinterpret_cast<fkvk::u32x4 *>(vb + ci * 8) = w;
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (tf + (e & 3) >= 0 && tf + (e & 3) < nq) vb[ci * 8 + e] = e8[e];
-                }
-            }
-        }
-    }
-}
-
-template <int R>
-__global__ __launch_bounds__(256, 6) void produce_kernel(ProduceArgs a) {
+// PAGES: pages per shrink workgroup, one or kShrinkPages.  What is written does not depend on it, to the bit.
+template <int R, int PAGES>
+__global__ __launch_bounds__(256, PAGES > 1 ? 6 : 2) void produce_kernel(ProduceArgs a) {
     constexpr int PS = 16, D = 128, HALF = D / 2;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -504,15 +391,72 @@ __global__ __launch_bounds__(256, 6) void produce_kernel(ProduceArgs a) {
     if (shrink_wg) {
         if constexpr (R > 0) {
             constexpr int RT = (R + 15) / 16, NT = 2 * RT;
-            __shared__ fkvk::f32x4 s_part[3][NT][kShrinkPages][64];
-            // tile u: page page0 + kShrinkPages lb + u; token slot col of it is call index tj0[u] + col
-            int64_t tj0[kShrinkPages];
-            bool tok_ok[kShrinkPages];
-            const uint16_t *xr[kShrinkPages];
-            fkvk::f32x4 acc[NT][kShrinkPages];
+            __shared__ fkvk::f32x4 s_part[3][NT][PAGES][64];
+            constexpr int KS = NT <= 2 ? 2 : 1;
+            if constexpr (PAGES == 1) {
+                // One page: the same steps in the same order for every wave as in the form below, so the
+                // sums have the same bits, but DEPTH of them in flight
+                constexpr int DEPTH = NT <= 4 ? 8 : 4;
+                const int64_t pp = page0 + lb, tj0 = pp * PS - pos0;
+                const bool ok = tj0 + col >= 0 && tj0 + col < nq;
+                const uint16_t *xr = a.x + (q.row0 + (ok ? tj0 + col : 0)) * a.hidden + 32 * KS * wave + 8 * grp;
+                const bool rok = R >= 16 || col < R;  // rows past r read row 0, zeroed
+                const uint16_t *ar = q.lora_a + (int64_t)(rok ? col : 0) * a.hidden + 32 * KS * wave + 8 * grp;
+                fkvk::u32x4 xa[DEPTH], bw[DEPTH][NT];
+                fkvk::f32x4 acc[NT];
 #pragma unroll
-            for (int u = 0; u < kShrinkPages; ++u) {
-                tj0[u] = (page0 + (int64_t)kShrinkPages * lb + u) * PS - pos0;
+                for (int t = 0; t < NT; ++t) acc[t] = fkvk::f32x4{0, 0, 0, 0};
+                auto load = [&](int d, int i) __attribute__((always_inline)) {
+                    const int off = 128 * KS * (i / KS) + 32 * (i % KS);
+                    xa[d] = ok ? fkvk::ldg128(xr + off) : fkvk::u32x4{0, 0, 0, 0};
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        bw[d][t] = fkvk::ldg128(ar + (int64_t)((t / RT) * R + 16 * (t % RT)) * a.hidden + off);
+                };
+                auto products = [&](int d) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        const fkvk::u32x4 w = rok ? bw[d][t] : fkvk::u32x4{0, 0, 0, 0};
+                        acc[t] = t < RT ? fkvk::mfma32(w, xa[d], acc[t]) : fkvk::mfma32(xa[d], w, acc[t]);
+                    }
+                };
+                const int steps = a.hidden / 128;  // of a wave: a multiple of eight
+#pragma unroll
+                for (int d = 0; d < DEPTH; ++d) load(d, d);
+                int i = DEPTH;
+                for (; i < steps; i += DEPTH)
+#pragma unroll
+                    for (int d = 0; d < DEPTH; ++d) {
+                        products(d);
+                        load(d, i + d);
+                    }
+#pragma unroll
+                for (int d = 0; d < DEPTH; ++d) products(d);
+                if (wave > 0) {
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) s_part[wave - 1][t][0][lane] = acc[t];
+                }
+                __syncthreads();
+                if (wave == 0) {
+                    uint16_t *pg = a.res_kv + (int64_t)q.bt_res[pp] * res_page_elems(PS, R);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        fkvk::f32x4 c = acc[t];
+#pragma unroll
+                        for (int w = 0; w < 3; ++w) c += s_part[w][t][0][lane];
+                        store_shrink<R>(c, t, pg, tj0, nq, col, grp);
+                    }
+                }
+                return;
+            }
+            // tile u: page page0 + PAGES lb + u; token slot col of it is call index tj0[u] + col
+            int64_t tj0[PAGES];
+            bool tok_ok[PAGES];
+            const uint16_t *xr[PAGES];
+            fkvk::f32x4 acc[NT][PAGES];
+#pragma unroll
+            for (int u = 0; u < PAGES; ++u) {
+                tj0[u] = (page0 + (int64_t)PAGES * lb + u) * PS - pos0;
                 const int64_t tok = tj0[u] + col;
                 tok_ok[u] = tok >= 0 && tok < nq;
                 xr[u] = a.x + q.row0 * a.hidden + (tok_ok[u] ? tok : 0) * a.hidden + 8 * grp;
@@ -534,32 +478,31 @@ __global__ __launch_bounds__(256, 6) void produce_kernel(ProduceArgs a) {
             // every load is unconditional and the wait counts stay exact).  Round k0 of wave w
             // covers hidden columns 4 k0 + w step .. + step - 1: the four waves' blocks of a round
             // are adjacent, so each token row is read in runs of 4 step columns.  Every A
-            // fragment serves the kShrinkPages token tiles.
-            constexpr int KS = NT <= 2 ? 2 : 1;
+            // fragment serves the PAGES token tiles.
             constexpr int step = 32 * KS;
-            auto load = [&](int k0, fkvk::u32x4 (&xa)[KS][kShrinkPages], fkvk::u32x4 (&bw)[KS][NT]) __attribute__((always_inline)) {
+            auto load = [&](int k0, fkvk::u32x4 (&xa)[KS][PAGES], fkvk::u32x4 (&bw)[KS][NT]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
                     const int off = 4 * k0 + wave * step + 32 * ks;
 #pragma unroll
-                    for (int u = 0; u < kShrinkPages; ++u)
+                    for (int u = 0; u < PAGES; ++u)
                         xa[ks][u] = tok_ok[u] ? fkvk::ldg128(xr[u] + off) : fkvk::u32x4{0, 0, 0, 0};
 #pragma unroll
                     for (int t = 0; t < NT; ++t) bw[ks][t] = fkvk::ldg128(ar[t] + off);
                 }
             };
-            auto products = [&](const fkvk::u32x4 (&xa)[KS][kShrinkPages], const fkvk::u32x4 (&bw)[KS][NT]) __attribute__((always_inline)) {
+            auto products = [&](const fkvk::u32x4 (&xa)[KS][PAGES], const fkvk::u32x4 (&bw)[KS][NT]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
                         const fkvk::u32x4 w = rok[t] ? bw[ks][t] : fkvk::u32x4{0, 0, 0, 0};
 #pragma unroll
-                        for (int u = 0; u < kShrinkPages; ++u)  // C_K^T (ranks in rows), C_V (tokens in rows)
+                        for (int u = 0; u < PAGES; ++u)  // C_K^T (ranks in rows), C_V (tokens in rows)
                             acc[t][u] = t < RT ? fkvk::mfma32(w, xa[ks][u], acc[t][u]) : fkvk::mfma32(xa[ks][u], w, acc[t][u]);
                     }
             };
-            fkvk::u32x4 xa0[KS][kShrinkPages], bw0[KS][NT], xa1[KS][kShrinkPages], bw1[KS][NT];
+            fkvk::u32x4 xa0[KS][PAGES], bw0[KS][NT], xa1[KS][PAGES], bw1[KS][NT];
             load(0, xa0, bw0);
             for (int k0 = 0;;) {
                 load(min(k0 + step, quarter - step), xa1, bw1);
@@ -573,14 +516,14 @@ __global__ __launch_bounds__(256, 6) void produce_kernel(ProduceArgs a) {
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
 #pragma unroll
-                    for (int u = 0; u < kShrinkPages; ++u) s_part[wave - 1][t][u][lane] = acc[t][u];
+                    for (int u = 0; u < PAGES; ++u) s_part[wave - 1][t][u][lane] = acc[t][u];
             }
             __syncthreads();
             if (wave == 0) {
 #pragma unroll
-                for (int u = 0; u < kShrinkPages; ++u) {
+                for (int u = 0; u < PAGES; ++u) {
                     if (tj0[u] >= nq) continue;  // page past the sequence's range: its table entry is not read
-                    const int64_t pp = page0 + (int64_t)kShrinkPages * lb + u;
+                    const int64_t pp = page0 + (int64_t)PAGES * lb + u;
                     uint16_t *pg = a.res_kv + (int64_t)q.bt_res[pp] * res_page_elems(PS, R);
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
@@ -672,8 +615,9 @@ __global__ __launch_bounds__(256, 6) void produce_kernel(ProduceArgs a) {
                 for (int e = 0; e < 8; ++e) {
                     const float c = cs[e >> 2][e & 3], s = sn[e >> 2][e & 3];
                     const float u = x0[e], w = x1[e];
-                    x0[e] = u * c - w * s;
-                    x1[e] = w * c + u * s;
+                    // written out: left to the compiler, which product is rounded first differs between instances
+                    x0[e] = __builtin_fmaf(u, c, -(w * s));
+                    x1[e] = __builtin_fmaf(u, s, w * c);
                 }
             }
             uint16_t *kb = pg + (h0 + hi) * blk + (t + 16 * b4) * 8;
@@ -711,114 +655,10 @@ __global__ __launch_bounds__(256, 6) void produce_kernel(ProduceArgs a) {
     }
 }
 
-// The same for calls of few pages (decode steps, short chunks): sixteen waves share one page's shrink,
-// each with every sixteenth 32-column step of the hidden dimension, KS steps requested together and
-// the next KS behind them, and the waves' partial tiles meet in LDS, where wave t adds up tile t.
-// Such a call is a chain of memory latencies: with four waves per four pages a hidden dimension of
-// 4096 is sixteen rounds of loads, here one or two (4 sequences of 64
-// tokens, rank 16: 24.4 -> 17.6 us; figures by size at wide_shrink).
-// Base workgroups run on the first four waves.
-constexpr int kWideWaves = 16;
 template <int R>
-__global__ __launch_bounds__(64 * kWideWaves) void produce_wide_kernel(ProduceArgs a) {
-    constexpr int PS = 16;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int col = lane & 15, grp = lane >> 4;
-    const int bid = blockIdx.x;
-    const bool shrink_wg = bid < a.n_shrink_blocks;
-    const ProduceSeq &q = a.seq[produce_seq(a, shrink_wg, bid)];
-    const int lb = bid - (shrink_wg ? q.first_shrink : q.first_base);
-    if (!shrink_wg) {
-        if (wave < 4) produce_base(a, q, lb, q.pos0, q.n, q.pos0 / PS);
-        return;
-    }
-    {
-        static_assert(R > 0, "nothing to shrink at rank 0");
-        constexpr int RT = (R + 15) / 16, NT = 2 * RT;
-        constexpr int SUMW = NT <= 4 ? kWideWaves : kWideWaves / 2;  // waves whose partials LDS holds at once
-        __shared__ fkvk::f32x4 s_part[SUMW][NT][64];
-        const int64_t nq = q.n, pp = q.pos0 / PS + lb;
-        const int64_t tj0 = pp * PS - q.pos0;
-        const int64_t tok = tj0 + col;
-        const bool tok_ok = tok >= 0 && tok < nq;
-        const uint16_t *xr = a.x + (q.row0 + (tok_ok ? tok : 0)) * a.hidden + 8 * grp;
-        const uint16_t *ar[NT];
-        const bool rok = R >= 16 || col < R;  // rows past r read row 0, zeroed
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-            ar[t] = q.lora_a + ((int64_t)((t / RT) * R + (rok ? 16 * (t % RT) + col : 0)) * a.hidden + 8 * grp);
-        constexpr int KS = NT <= 2 ? 4 : (NT <= 4 ? 2 : 1);
-        const int steps = a.hidden / (32 * kWideWaves);  // per wave, at least two
-        fkvk::f32x4 acc[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = fkvk::f32x4{0, 0, 0, 0};
-        // steps past the last re-read it and are not multiplied
-        auto load = [&](int k0, fkvk::u32x4 (&xa)[KS], fkvk::u32x4 (&bw)[KS][NT]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int off = 32 * (kWideWaves * min(k0 + ks, steps - 1) + wave);
-                xa[ks] = tok_ok ? fkvk::ldg128(xr + off) : fkvk::u32x4{0, 0, 0, 0};
-#pragma unroll
-                for (int t = 0; t < NT; ++t) bw[ks][t] = fkvk::ldg128(ar[t] + off);
-            }
-        };
-        auto products = [&](int k0, const fkvk::u32x4 (&xa)[KS], const fkvk::u32x4 (&bw)[KS][NT]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                if (k0 + ks >= steps) break;
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const fkvk::u32x4 w = rok ? bw[ks][t] : fkvk::u32x4{0, 0, 0, 0};
-                    acc[t] = t < RT ? fkvk::mfma32(w, xa[ks], acc[t]) : fkvk::mfma32(xa[ks], w, acc[t]);
-                }
-            }
-        };
-        fkvk::u32x4 xa0[KS], bw0[KS][NT], xa1[KS], bw1[KS][NT];
-        load(0, xa0, bw0);
-        for (int k0 = 0;;) {
-            load(k0 + KS, xa1, bw1);
-            products(k0, xa0, bw0);
-            if ((k0 += KS) >= steps) break;
-            load(k0 + KS, xa0, bw0);
-            products(k0, xa1, bw1);
-            if ((k0 += KS) >= steps) break;
-        }
-        if constexpr (SUMW < kWideWaves) {
-            if (wave >= SUMW) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t) s_part[wave - SUMW][t][lane] = acc[t];
-            }
-            __syncthreads();
-            if (wave < SUMW) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t) acc[t] += s_part[wave][t][lane];
-            }
-            __syncthreads();
-        }
-        if (wave < SUMW) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t) s_part[wave][t][lane] = acc[t];
-        }
-        __syncthreads();
-        if (wave < NT) {
-            fkvk::f32x4 c = s_part[0][wave][lane];
-#pragma unroll
-            for (int w = 1; w < SUMW; ++w) c += s_part[w][wave][lane];
-            store_shrink<R>(c, wave, a.res_kv + (int64_t)q.bt_res[pp] * res_page_elems(PS, R), tj0, nq, col, grp);
-        }
-    }
-}
-
-template <int R>
-void launch_produce(const ProduceArgs &a, unsigned blocks, bool wide, hipStream_t st) {
-    if constexpr (R > 0) {
-        if (wide) {
-            hipLaunchKernelGGL(produce_wide_kernel<R>, dim3(blocks), dim3(64 * kWideWaves), 0, st, a);
-            return;
-        }
-    }
-    hipLaunchKernelGGL(produce_kernel<R>, dim3(blocks), dim3(256), 0, st, a);
+void launch_produce(const ProduceArgs &a, unsigned blocks, int pages, hipStream_t st) {
+    if (R > 0 && pages > 1) hipLaunchKernelGGL((produce_kernel<R, R == 0 ? 1 : kShrinkPages>), dim3(blocks), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((produce_kernel<R, 1>), dim3(blocks), dim3(256), 0, st, a);
 }
 }  // namespace
 
@@ -923,61 +763,59 @@ fkv_status fkv_produce_tokens_batch(const fkv_produce_seq *seqs, int32_t nseq, c
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t n_hg = (hkv + kProdHeads - 1) / kProdHeads;
-    auto pages_of = [&](const fkv_produce_seq &q) {  // pages the sequence's range touches
-        return q.n == 0 ? (int64_t)0 : (q.pos0 + q.n - 1) / page_size - q.pos0 / page_size + 1;
-    };
-    auto shrinks = [&](const fkv_produce_seq &q) { return r > 0 && q.lora_a && q.n > 0; };
-    auto is_small = [&](const fkv_produce_seq &q) { return wide_shrink(pages_of(q), q.n, r); };
     for (int32_t c0 = 0; c0 < nseq; c0 += kProdMaxSeqs) {
+        ProduceArgs a{};
+        a.hidden = hidden;
+        a.hkv = hkv;
+        a.x = static_cast<const uint16_t *>(x);
+        a.k_raw = static_cast<const uint16_t *>(k_raw);
+        a.v = static_cast<const uint16_t *>(v);
+        a.rope_cos = rope_cos;
+        a.rope_sin = rope_sin;
+        a.base_kv = static_cast<uint16_t *>(base_kv);
+        a.res_kv = static_cast<uint16_t *>(res_kv);
+        auto pages_of = [&](const fkv_produce_seq &q) {  // pages that its range touches
+            return q.n == 0 ? (int64_t)0 : (q.pos0 + q.n - 1) / page_size - q.pos0 / page_size + 1;
+        };
         const int32_t c1 = std::min(nseq, c0 + kProdMaxSeqs);
-        bool any_wide = false;
-        for (int32_t i = c0; i < c1; ++i) any_wide |= shrinks(seqs[i]) && is_small(seqs[i]);
-        // the sequences of few pages (those without shrink only beside others), then the rest
-        for (const bool wide : {true, false}) {
-            if (wide && !any_wide) continue;
-            ProduceArgs a{};
-            a.hidden = hidden;
-            a.hkv = hkv;
-            a.x = static_cast<const uint16_t *>(x);
-            a.k_raw = static_cast<const uint16_t *>(k_raw);
-            a.v = static_cast<const uint16_t *>(v);
-            a.rope_cos = rope_cos;
-            a.rope_sin = rope_sin;
-            a.base_kv = static_cast<uint16_t *>(base_kv);
-            a.res_kv = static_cast<uint16_t *>(res_kv);
-            const int64_t per_wg = wide ? 1 : kShrinkPages;
-            int64_t n_shrink = 0, n_base = 0;
-            for (int32_t i = c0; i < c1; ++i) {
-                const fkv_produce_seq &q = seqs[i];
-                if (q.n == 0 || wide != (any_wide && is_small(q))) continue;
-                const int64_t pages = pages_of(q);
-                ProduceSeq &o = a.seq[a.nseq++];
-                o.bt_base = q.bt_base;
-                o.bt_res = q.bt_res;
-                o.lora_a = r > 0 ? static_cast<const uint16_t *>(q.lora_a) : nullptr;
-                o.pos0 = q.pos0;
-                o.row0 = q.row0;
-                o.n = (int32_t)q.n;
-                o.first_shrink = (int32_t)n_shrink;
-                o.first_base = (int32_t)n_base;  // offset by the shrink count below
-                if (o.lora_a) n_shrink += (pages + per_wg - 1) / per_wg;
-                n_base += pages * n_hg;
-            }
-            if (a.nseq == 0) continue;
-            if (n_shrink + n_base > INT32_MAX) return fkv::fail(FKV_ERR_INVALID, "fkv_produce_tokens: batch too large");
-            for (int32_t j = 0; j < a.nseq; ++j) a.seq[j].first_base += (int32_t)n_shrink;
-            a.n_shrink_blocks = (int32_t)n_shrink;
-            const unsigned blocks = (unsigned)(n_shrink + n_base);
-            switch (r) {
-            case 0: launch_produce<0>(a, blocks, wide, st); break;
-            case 8: launch_produce<8>(a, blocks, wide, st); break;
-            case 16: launch_produce<16>(a, blocks, wide, st); break;
-            case 32: launch_produce<32>(a, blocks, wide, st); break;
-            default: launch_produce<64>(a, blocks, wide, st); break;
-            }
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return fkv::fail(FKV_ERR_HIP, std::string("fkv_produce_tokens: ") + hipGetErrorString(e));
+        int64_t longest = 0, total = 0;
+        for (int32_t i = c0; i < c1; ++i) {
+            if (r == 0 || !seqs[i].lora_a) continue;
+            longest = std::max(longest, pages_of(seqs[i]));
+            total += pages_of(seqs[i]);
         }
+        const int per_wg = one_page_shrink(longest, total, r) ? 1 : kShrinkPages;
+        int64_t n_shrink = 0, n_base = 0;
+        for (int32_t i = c0; i < c1; ++i) {
+            const fkv_produce_seq &q = seqs[i];
+            if (q.n == 0) continue;
+            const int64_t pages = pages_of(q);
+            ProduceSeq &o = a.seq[a.nseq++];
+            o.bt_base = q.bt_base;
+            o.bt_res = q.bt_res;
+            o.lora_a = r > 0 ? static_cast<const uint16_t *>(q.lora_a) : nullptr;
+            o.pos0 = q.pos0;
+            o.row0 = q.row0;
+            o.n = (int32_t)q.n;
+            o.first_shrink = (int32_t)n_shrink;
+            o.first_base = (int32_t)n_base;  // offset by the shrink count below
+            if (o.lora_a) n_shrink += (pages + per_wg - 1) / per_wg;
+            n_base += pages * n_hg;
+        }
+        if (a.nseq == 0) continue;
+        if (n_shrink + n_base > INT32_MAX) return fkv::fail(FKV_ERR_INVALID, "fkv_produce_tokens: batch too large");
+        for (int32_t j = 0; j < a.nseq; ++j) a.seq[j].first_base += (int32_t)n_shrink;
+        a.n_shrink_blocks = (int32_t)n_shrink;
+        const unsigned blocks = (unsigned)(n_shrink + n_base);
+        switch (r) {
+        case 0: launch_produce<0>(a, blocks, per_wg, st); break;
+        case 8: launch_produce<8>(a, blocks, per_wg, st); break;
+        case 16: launch_produce<16>(a, blocks, per_wg, st); break;
+        case 32: launch_produce<32>(a, blocks, per_wg, st); break;
+        default: launch_produce<64>(a, blocks, per_wg, st); break;
+        }
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return fkv::fail(FKV_ERR_HIP, std::string("fkv_produce_tokens: ") + hipGetErrorString(e));
     }
     return FKV_OK;
 }

@@ -232,7 +232,7 @@ def test_producer_batch_over_32_sequences():
 @pytest.mark.parametrize("r", [8, 16, 32, 64])
 @pytest.mark.parametrize("hidden", [1024, 3072])
 def test_producer_on_both_sides_of_eight_pages(r, hidden):
-    """Sequences of 1, 8, 9 and 10 pages (eight is the most that sixteen waves take one page at a
+    """Sequences of 1, 8, 9 and 10 pages (eight is the most that workgroups take one page at a
     time) with and without an adapter, in one call: each as a call of its own writes it, and as the
     oracle does.  Hidden 3072 is six steps per wave, not a multiple of the steps requested together."""
     hkv, d, ps = 2, 128, 16
@@ -264,3 +264,30 @@ def test_producer_on_both_sides_of_eight_pages(r, hidden):
     assert torch.equal(base_batch[:, 1].view(torch.int16), base_ref[:, 1].view(torch.int16)), "V"
     _within_one_ulp(base_batch[:, 0], base_ref[:, 0], f"K r={r}", _rope_slack(k))
     _compare_c(res_batch, res_ref, segs, r, f"r={r} hidden={hidden}")
+
+
+@pytest.mark.parametrize("r", [8, 16, 32, 64])
+@pytest.mark.parametrize("hidden", [1024, 3072])
+def test_producer_writes_the_same_bits_however_a_sequence_is_cut(r, hidden):
+    """150 tokens in one call (ten pages: four pages per workgroup) and cut into calls of one to eight
+    pages (one page per workgroup), the last of them beside a long sequence: the same bits."""
+    hkv, d, ps, pos0, n = 2, 128, 16, 7, 150
+    print(f"case producer cuts r={r} hidden={hidden}", flush=True)
+    x, k, v, a, base0, res0, tables, bts = _batch_case([(pos0, n, True), (3, 200, True)], hkv, d, ps, r, hidden, 700 + r, True)
+    xg, kg, vg = _bf16(x), _bf16(k), _bf16(v)
+    ag = [_bf16(ai) for ai in a]
+    whole = [base0.clone(), res0.clone()]
+    rt.produce_tokens_batch([(bts[0], bts[0], ag[0], pos0, n, 0), (bts[1], bts[1], ag[1], 3, 200, n)], xg, kg, vg, tables,
+                            *whole, hkv, d, r, ps)
+    cut, at = [base0.clone(), res0.clone()], 0
+    for m in [1, 8, 17, 100, 24]:
+        seqs = [(bts[0], bts[0], ag[0], pos0 + at, m, at)]
+        if at + m == n:
+            seqs.append((bts[1], bts[1], ag[1], 3, 200, n))
+        rt.produce_tokens_batch(seqs, xg, kg, vg, tables, *cut, hkv, d, r, ps)
+        at += m
+    torch.cuda.synchronize()
+    assert at == n
+    for w, c in zip(whole, cut):
+        same = bool(torch.equal(w.view(torch.int16), c.view(torch.int16)))
+        assert same
