@@ -102,20 +102,27 @@ __device__ __forceinline__ uint32_t opaque(uint32_t a) {
 // offset moves the source and the destination alike): lane i's 16 bytes at voff = 16 i.  Written as
 // an instruction because the compiler waits for every copy it knows of before any later LDS read;
 // the waits here are the counted ones of the hand-over.
-// (m0, which holds the destination, is used by nothing else in this file.)
+// The source goes through a scalar move inside the instruction group: a vector-memory instruction may
+// not read a scalar register within five states of the vector instruction that wrote it (readfirstlane,
+// readlane), which the compiler does not check for operands of its own making here.  The move is also the
+// state that has to pass between the write of m0 and its use.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // m0 is named although the compiler does not allocate it
 template <int I>
 __device__ __forceinline__ void dma_kb(uint64_t base, uint32_t dst, uint32_t voff) {
     base = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base) |
            (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32;
     dst = (uint32_t)__builtin_amdgcn_readfirstlane((int)dst);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
-                 ::"s"(dst), "v"(voff), "s"(base), "n"(I * 1024) : "memory");
+    uint64_t src;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0 offset:%4"
+                 : "=&s"(src) : "s"(dst), "v"(voff), "s"(base), "n"(I * 1024) : "memory", "m0");
 }
 // Copy of 64 x 16 bytes, lane i's from its own address, to dst + 16 i.
 __device__ __forceinline__ void dma_1kb_at(uint64_t addr, uint32_t dst) {
     dst = (uint32_t)__builtin_amdgcn_readfirstlane((int)dst);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(addr) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(addr) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 template <int R, int G, bool ROPE, int NW>
 __device__ __forceinline__ void prefill_block(const PrefillArgs &p, unsigned char *lds, int a, int h, int tok_begin) {
