@@ -9,6 +9,7 @@ import pytest
 import torch
 
 import oracle
+from paper_2604_06370_amd import _native as N
 from paper_2604_06370_amd import workloads as W
 from paper_2604_06370_amd.driver import LoadedWorkload
 
@@ -235,4 +236,37 @@ def test_prefill_amplified_adapters(r, rope, hq, hkv, n_agents):
     wl = W.fanout(f"pf-amp-r{r}", 95, n_agents=n_agents, prefix=600, suffix_lo=1, suffix_hi=60, hq=hq, hkv=hkv, r=r,
                   chunk=45, b_std=1.0 / np.sqrt(r))
     lw, g, ref = run_prefill(f"prefill amplified r={r} rope={rope} hq={hq} hkv={hkv} agents={n_agents}", wl, rope)
+    lw.close()
+
+
+def _block_rows(wl, rope):
+    return N.fkv_prefill_block_rows(wl.hq, wl.hkv, wl.r, int(rope), wl.n_agents, max(len(c) for c in wl.chunk_tokens), None)
+
+
+@pytest.mark.parametrize("r,rope", [(0, False), (8, False), (8, True), (16, False), (16, True), (32, False), (32, True), (64, False)])
+@pytest.mark.parametrize("hq,hkv", [(8, 2), (16, 2)])
+def test_prefill_long_contexts_in_blocks_of_128_rows(r, rope, hq, hkv):
+    """The page ids of 64 tiles at a time and their delay line, whose length depends on rank and RoPE,
+    roll over: sequences that end on both sides of tiles 64 and 128.  Residuals as large as the base
+    rows, so that a tile's page taken from the wrong place moves the output by a tenth (rel-L2)."""
+    end, chunk = [4095, 4097, 4161, 8192, 8200, 8257], [3, 33, 20, 1, 40, 7]
+    wl = W._build("pf-long", 96, hq, hkv, 128, r, 16, [-1], [3900], [0] * 6, [e - c - 3900 for e, c in zip(end, chunk)], chunk,
+                  {1} if r else set(), 1.0 / np.sqrt(max(r, 1)))
+    assert _block_rows(wl, rope) == 128
+    lw, g, ref = run_prefill(f"long r={r} rope={rope} hq={hq}", wl, rope, q_sample=lambda n: sorted({0, n // 2, n - 1}))
+    lw.close()
+
+
+@pytest.mark.parametrize("r,rope", [(0, False), (8, False), (8, True), (16, False), (16, True), (32, False)])
+@pytest.mark.parametrize("hq,hkv", [(8, 2), (16, 2)])
+def test_prefill_long_contexts_in_blocks_of_256_rows(r, rope, hq, hkv):
+    """The same on grids that take 256 rows per workgroup: chunks of seventeen blocks and more that begin
+    below tile 64 and end behind it, with four and eight query heads per KV head."""
+    n = 17 * 256 // (hq // hkv)
+    chunk = [n + 9, n // 3, n - 50]
+    wl = W._build("pf-long-256", 97, hq, hkv, 128, r, 16, [-1], [3700], [0] * 3, [100, 400, 7], chunk, {1} if r else set(),
+                  1.0 / np.sqrt(max(r, 1)))
+    assert _block_rows(wl, rope) == 256
+    sample = lambda m: sorted({0, 31, 32, 63, 64, m // 2, 4096 - 3800, 4097 - 3800, m - 65, m - 2, m - 1} & set(range(m)))
+    lw, g, ref = run_prefill(f"long-256 r={r} rope={rope} hq={hq}", wl, rope, q_sample=sample)
     lw.close()
