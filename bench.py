@@ -8,7 +8,9 @@ over all 16 agents; tokens/s = agents x steps / wall time of the timed steps.
 
 The headline runs the method as the key reconstruction K = K_base + C_K B_K (no
 position rotation of the rebuilt term); the same workload with deferred RoPE on the
-rebuilt term is timed afterwards and reported under "rope_on".
+rebuilt term is timed afterwards and reported under "rope_on".  The result line on stdout
+carries the headline, rope_on, prefill and the producer; every other workload and the whole entries
+go to stderr (one "# name {...}" line each, then "# detail").
 
 Inputs are resident in HBM before timing starts.  Three independent copies of the
 caches are built and the steps rotate over them, so consecutive steps never read
@@ -193,6 +195,34 @@ def measure_producer(lw, wl, agents, dev, stream, steps: int = 5, hidden: int = 
             "bound": "hbm", "achieved_GBps": gbs, "frac": gbs / HBM_PEAK_GBS}
 
 
+def prefill_kernel(wl, agents, rope: bool) -> str:
+    """The kernel that the prefill entry point chooses for these agents' chunks."""
+    import ctypes
+    from paper_2604_06370_amd import _native as N
+    pipelined = ctypes.c_int32(0)
+    N.fkv_prefill_block_rows(wl.hq, wl.hkv, wl.r, int(rope), len(agents), max(wl.n_queries(a) for a in agents),
+                             ctypes.byref(pipelined))
+    return "prefill_stream_kernel" if pipelined.value else "prefill_rebuild_kernel"
+
+
+def brief(entry: dict) -> dict:
+    """The figures of one measurement that the result line carries; the whole entry goes to stderr."""
+    if "error" in entry:
+        return {"error": entry["error"][:120]}
+    out = {}
+    for key, name, scale in (("kernel_ms", "kernel_us", 1e3), ("combine_ms", "combine_us", 1e3), ("frac", "frac", 1),
+                             ("value", "tokens_per_s", 1), ("tokens_per_s", "tokens_per_s", 1), ("us_per_step", "us", 1),
+                             ("host_build_serialise_ms", "host_ms", 1), ("GBps", "GBps", 1), ("traffic", "traffic", 1)):
+        if entry.get(key) is not None:
+            out[name] = float("%.4g" % (entry[key] * scale))
+    for key, v in entry.items():
+        if isinstance(v, dict) and key in ("rope_off", "rope_on", "eager", "graph", "copy", "sum"):
+            out[key] = brief(v)
+        elif key.endswith("_ms") and key.split("_")[0] in ("sequential", "two", "graph", "decode", "prefill"):
+            out[key] = float("%.4g" % v)
+    return out
+
+
 def measure_prefill(args, dev, stream) -> dict:
     """Chunked prefill on one workload (default: 16 agents append 2048-token chunks after a
     32768-token shared prefix), RoPE off and on; bound by the matrix cores."""
@@ -230,7 +260,7 @@ def measure_prefill(args, dev, stream) -> dict:
         k_ms = float(ms.mean())
         tflops = fl["total"] / (k_ms * 1e-3) / 1e12
         res["rope_on" if rope else "rope_off"] = {
-            "kernel": "prefill_kernel" if rope and wl.r > 32 else "prefill_stream_kernel", "kernel_ms": k_ms, "kernel_ms_p10_p50_p90": [float(np.percentile(ms, q)) for q in (10, 50, 90)],
+            "kernel": prefill_kernel(wl, agents, rope), "kernel_ms": k_ms, "kernel_ms_p10_p50_p90": [float(np.percentile(ms, q)) for q in (10, 50, 90)],
             "tokens_per_s": fl["rows"] * n / (t1 - t0), "achieved": tflops, "frac": tflops / MFMA_BF16_PEAK_TFLOPS}
         if rope:
             res["producer"] = measure_producer(lw, wl, agents, dev, stream)
@@ -593,34 +623,41 @@ def main():
         "roofline": {"bound": "hbm", "achieved": h["achieved_GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": h["frac"], "traffic": counter_traffic(rope, wl.name, h["pages_per_split"]),
                      "kernel": h["kernel"], "algorithmic_bytes": h["algorithmic_bytes"], "kernel_ms": split_avg,
-                     "kernel_ms_p10_p50_p90": h["kernel_ms_p10_p50_p90"], "combine_ms": h["combine_ms"],
-                     "call_GBps": call_gbs},
-        "bytes": h["bytes"],
+                     "kernel_ms_p10_p50_p90": [round(x, 5) for x in h["kernel_ms_p10_p50_p90"]],
+                     "combine_ms": round(h["combine_ms"], 5), "call_GBps": round(call_gbs, 1)},
     }
+    detail = {"headline": h}  # whole entries, for stderr; the result line stays below 2000 characters
     if copy_probe is not None:
         out["copy_probe"] = copy_probe
     if not args.no_rope_on and not rope and wl.r > 0:
         q = decode_entry(wl, dev, stream, True, args.steps, args.warmup, args.copies, args.pps, args.item_agents,
                          args.event_every, agents)
         q["traffic"] = counter_traffic(True, wl.name, q["pages_per_split"])
-        out["rope_on"] = q
+        detail["rope_on"] = q
     try:
-        out["plan"] = {"rope_off": plan_cost(wl, dev, False), "rope_on": plan_cost(wl, dev, True)}
+        detail["plan"] = {"rope_off": plan_cost(wl, dev, False), "rope_on": plan_cost(wl, dev, True)}
     except Exception as e:
-        out["plan"] = {"error": f"{type(e).__name__}: {e}"}
+        detail["plan"] = {"error": f"{type(e).__name__}: {e}"}
     if not args.no_prefill:
-        out["prefill"] = measure_prefill(args, dev, stream)
-        out["producer"] = out["prefill"].pop("producer")
-    if not args.no_suite:
-        out["workloads"] = suite(args, dev, stream)
+        detail["prefill"] = measure_prefill(args, dev, stream)
+        detail["producer"] = detail["prefill"].pop("producer")
     if args.stream_probe_mb > 0:
-        out["stream_probe"] = stream_probe(dev, args.stream_probe_mb)
+        detail["stream_probe"] = stream_probe(dev, args.stream_probe_mb)
+    for name in ("rope_on", "prefill", "producer"):
+        if name in detail:
+            out[name] = brief(detail[name])
+    if not args.no_suite:
+        detail["workloads"] = suite(args, dev, stream)
+        for name, entry in detail["workloads"].items():
+            print(f"# {name} {json.dumps(brief(entry))}", file=sys.stderr, flush=True)
     if not args.no_cpu_baseline:
         print("# timing the CPU oracle on a bounded sample", file=sys.stderr, flush=True)
         cb = cpu_baseline(wl, agents, rope)
         cb["cpu_model"] = cpu_model()
         cb["logical_cpus"] = os.cpu_count()
         out["cpu_baseline"] = cb
+    for name, entry in detail.items():
+        print(f"# detail {name} {json.dumps(entry)}", file=sys.stderr, flush=True)
     print(json.dumps(out))
 
 
