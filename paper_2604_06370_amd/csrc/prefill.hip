@@ -42,7 +42,7 @@ constexpr int TILE_KEYS = 64;              // four pages
 constexpr float kNegInf = -INFINITY;
 
 // ---------------------------------------------------------------------------
-// Streaming kernel.  A workgroup of eight waves holds 256 query rows, and 64-key tiles
+// Rebuild kernel.  A workgroup of eight waves holds 256 query rows, and 64-key tiles
 // stream through a ring of LDS buffers by direct memory-to-LDS copies: wave w < 4 copies
 // the K block (and, with an adapter, the rCache page) of page w of a tile, wave 4 + w its
 // V block.  One barrier per tile hands a buffer over: every wave has waited (by count)
@@ -79,16 +79,16 @@ struct RebuildShape {
     static constexpr int K_OFF = 0;
     static constexpr int V_OFF = 4 * 4096;
     static constexpr int C_OFF = 8 * 4096;
-    // RoPE on: table rows [page][half][cos m, cos m + 1, sin m, sin m + 1][1 KB], m = 2 half
+    // table rows [page][half][cos m, cos m + 1, sin m, sin m + 1][1 KB], m = 2 half
     static constexpr int T_OFF = C_OFF + 4 * RT * 1024;
-    // RoPE on: [page pw][half][cos, sin][frequency tile j][lane group] 16 B
+    // [page pw][half][cos, sin][frequency tile j][lane group] 16 B
     static constexpr int BUF_BYTES = T_OFF + 4 * 2 * 256;
     static constexpr int SBV_BYTES = R * D * 4;
     static constexpr int SACC_BYTES = kStreamRows * R * 4;
     static constexpr int EPI_BYTES = SBV_BYTES + SACC_BYTES;
     static constexpr int RING_BYTES = NBUF * BUF_BYTES;
     static constexpr int MAIN_BYTES = RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES;
-    // RoPE on: cos then sin of positions 0..15 in the table's own order ([tile m][lane] 16 B)
+    // cos then sin of positions 0..15 in the table's own order ([tile m][lane] 16 B)
     static constexpr int COLT_BYTES = 2 * 4096;
     static constexpr int LDS_BYTES = MAIN_BYTES + SBK_BYTES + COLT_BYTES;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of one workgroup");
@@ -165,25 +165,21 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
         LdsU32x4 *dst = b + ((kwave ? S::K_OFF : S::V_OFF) + pw * 4096) / 16;
 #pragma unroll
         for (int i = 0; i < 4; ++i) lds_dma16(rs, lane * 16 + i * 1024, dst + i * 64);
-        if constexpr (R > 0) {
-            if (res_copy) {
-                const i32x4 rc = block_rsrc(reinterpret_cast<uint64_t>(p.res_kv + (int64_t)idr * (RT * 512)), RT * 1024);
+        if (res_copy) {
+            const i32x4 rc = block_rsrc(reinterpret_cast<uint64_t>(p.res_kv + (int64_t)idr * (RT * 512)), RT * 1024);
 #pragma unroll
-                for (int t = 0; t < RT; ++t) lds_dma16(rc, lane * 16 + t * 1024, b + (S::C_OFF + (t * 4 + pw) * 1024) / 16);
-            }
+            for (int t = 0; t < RT; ++t) lds_dma16(rc, lane * 16 + t * 1024, b + (S::C_OFF + (t * 4 + pw) * 1024) / 16);
         }
-        {
-            if (use_res) {
-                // cos and sin at the first position of page pw for the frequencies this wave's
-                // rebuild uses: lane 4j + g (< 8) copies the 16 bytes that lane group g holds in
-                // frequency tile 2 half + j of the page's first table row
-                const int pg = min(tile * 4 + pw, n_pages - 1);
-                const int voff = ((pg * (PS * D / 2) + (2 * half + (lane >> 2)) * 256) + 64 * (lane & 3)) * 4;
-                LdsU32x4 *td = b + (S::T_OFF + (pw * 2 + half) * 256) / 16;
-                if (lane < 8) {
-                    lds_dma16(rope_rc, voff, td);
-                    lds_dma16(rope_rs, voff, td + 8);
-                }
+        if (use_res) {
+            // cos and sin at the first position of page pw for the frequencies this wave's
+            // rebuild uses: lane 4j + g (< 8) copies the 16 bytes that lane group g holds in
+            // frequency tile 2 half + j of the page's first table row
+            const int pg = min(tile * 4 + pw, n_pages - 1);
+            const int voff = ((pg * (PS * D / 2) + (2 * half + (lane >> 2)) * 256) + 64 * (lane & 3)) * 4;
+            LdsU32x4 *td = b + (S::T_OFF + (pw * 2 + half) * 256) / 16;
+            if (lane < 8) {
+                lds_dma16(rope_rc, voff, td);
+                lds_dma16(rope_rs, voff, td + 8);
             }
         }
     };
@@ -213,34 +209,31 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
             qf[nt][kk] = v;
         }
     }
-    // RoPE on: B_K^T fragments of the agent's adapter (lane holds B_K[16t + 4grp + i][h*D +
+    // B_K^T fragments of the agent's adapter (lane holds B_K[16t + 4grp + i][h*D +
     // 16mt + col]) in LDS for the whole launch; this wave rebuilds u tiles 2 half, 2 half + 1
     // and their rotation partners + 4 of page pw, with the table rows of frequency tiles
     // 2 half + j, loaded one tile ahead
-    {
-        if (use_res) {
-            u32x2 *bkt = const_cast<u32x2 *>(sBK);
-            const uint16_t *bk = p.lora_b + (int64_t)ad * 2 * R * n + (int64_t)h * D;
-            for (int idx = threadIdx.x; idx < RT * 8 * 64; idx += 64 * kStreamWaves) {
-                const int ln = idx & 63, rest = idx >> 6;
-                const int mt = rest & 7, t = rest >> 3;
-                const int c = ln & 15, gg = ln >> 4;
-                uint32_t w[2];
+    if (use_res) {
+        u32x2 *bkt = const_cast<u32x2 *>(sBK);
+        const uint16_t *bk = p.lora_b + (int64_t)ad * 2 * R * n + (int64_t)h * D;
+        for (int idx = threadIdx.x; idx < RT * 8 * 64; idx += 64 * kStreamWaves) {
+            const int ln = idx & 63, rest = idx >> 6;
+            const int mt = rest & 7, t = rest >> 3;
+            const int c = ln & 15, gg = ln >> 4;
+            uint32_t w[2];
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int r0 = 16 * t + 4 * gg + 2 * j;
-                    const uint16_t lo = r0 < R ? bk[(int64_t)r0 * n + 16 * mt + c] : (uint16_t)0;
-                    const uint16_t hi = r0 + 1 < R ? bk[(int64_t)(r0 + 1) * n + 16 * mt + c] : (uint16_t)0;
-                    w[j] = (uint32_t)lo | ((uint32_t)hi << 16);
-                }
-                bkt[idx] = u32x2{w[0], w[1]};
+            for (int j = 0; j < 2; ++j) {
+                const int r0 = 16 * t + 4 * gg + 2 * j;
+                const uint16_t lo = bk[(int64_t)r0 * n + 16 * mt + c], hi = bk[(int64_t)(r0 + 1) * n + 16 * mt + c];
+                w[j] = (uint32_t)lo | ((uint32_t)hi << 16);
             }
-            __syncthreads();  // B_K^T fragments written (no copy into LDS is in flight yet)
-            // cos and sin of positions 0..15 (the first 4 KB of each table): wave w copies
-            // kilobyte w % 4 of cos (w < 4) or sin; they land before the first tile's barrier
-            LdsU32x4 *colt = (LdsU32x4 *)(lds + (S::MAIN_BYTES + S::SBK_BYTES) / 16);
-            lds_dma16(wave < 4 ? rope_rc : rope_rs, lane * 16 + (wave & 3) * 1024, colt + wave * 64);
+            bkt[idx] = u32x2{w[0], w[1]};
         }
+        __syncthreads();  // B_K^T fragments written (no copy into LDS is in flight yet)
+        // cos and sin of positions 0..15 (the first 4 KB of each table): wave w copies
+        // kilobyte w % 4 of cos (w < 4) or sin; they land before the first tile's barrier
+        LdsU32x4 *colt = (LdsU32x4 *)(lds + (S::MAIN_BYTES + S::SBK_BYTES) / 16);
+        lds_dma16(wave < 4 ? rope_rc : rope_rs, lane * 16 + (wave & 3) * 1024, colt + wave * 64);
     }
     // the page ids must be in registers before the first copies read them
     wait_vmcnt<0>();
@@ -359,7 +352,7 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
                 }
 #pragma unroll
                 for (int t = 0; t < RT; ++t) {
-                    ck[t] = (16 * t + 4 * grp < R) ? u32x2{c[t].x, c[t].y} : u32x2{0, 0};
+                    ck[t] = u32x2{c[t].x, c[t].y};
 #pragma unroll
                     for (int j = 0; j < 4; ++j) u[j] = mfma16(bkf[t][j], ck[t], u[j]);
                 }
@@ -509,25 +502,22 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
             // row sums of the bf16 weights (every accumulator row holds the sum)
             lacc[0] = mfma32(kOnes, pb0, lacc[0]);
             lacc[1] = mfma32(kOnes, pb1, lacc[1]);
-            if constexpr (R > 0) {
-                if (use_res) {
+            if (use_res) {
 #pragma unroll
-                    for (int t = 0; t < RT; ++t) {
-                        // C_V of rank 16t + col, tokens 4grp .. +3 of the two pages (.zw)
-                        u32x4 cf[2];
-                        lds_get2<S::CV>(base + S::C_OFF + (t * 4 + 2 * half) * 1024, cf);
-                        u32x2 c0 = u32x2{cf[0].z, cf[0].w};
-                        u32x2 c1 = u32x2{cf[1].z, cf[1].w};
-                        if (ragged) {
-                            const int vis0 = L - (tile * 4 + 2 * half) * PS;
-                            c0 = mask4(c0, vis0, grp);
-                            c1 = mask4(c1, vis0 - PS, grp);
-                        }
-                        const bool vvalid = 16 * t + col < R;
-                        const u32x4 ca = vvalid ? u32x4{c0.x, c0.y, c1.x, c1.y} : u32x4{0, 0, 0, 0};
-                        racc[t][0] = mfma32(ca, pb0, racc[t][0]);
-                        racc[t][1] = mfma32(ca, pb1, racc[t][1]);
+                for (int t = 0; t < RT; ++t) {
+                    // C_V of rank 16t + col, tokens 4grp .. +3 of the two pages (.zw)
+                    u32x4 cf[2];
+                    lds_get2<S::CV>(base + S::C_OFF + (t * 4 + 2 * half) * 1024, cf);
+                    u32x2 c0 = u32x2{cf[0].z, cf[0].w};
+                    u32x2 c1 = u32x2{cf[1].z, cf[1].w};
+                    if (ragged) {
+                        const int vis0 = L - (tile * 4 + 2 * half) * PS;
+                        c0 = mask4(c0, vis0, grp);
+                        c1 = mask4(c1, vis0 - PS, grp);
                     }
+                    const u32x4 ca = u32x4{c0.x, c0.y, c1.x, c1.y};
+                    racc[t][0] = mfma32(ca, pb0, racc[t][0]);
+                    racc[t][1] = mfma32(ca, pb1, racc[t][1]);
                 }
             }
         }
@@ -537,31 +527,26 @@ __global__ __launch_bounds__(64 * kStreamWaves, 1) void prefill_rebuild_kernel(P
 
     // ---- epilogue: O = (acc + acc_r . B_V[h]) / l ----
     const float l_run[2] = {lacc[0][0], lacc[1][0]};
-    if constexpr (R > 0) {
-        if (use_res) {
-            const uint16_t *bv = p.lora_b + ((int64_t)ad * 2 + 1) * R * n + (int64_t)h * D;
-            for (int e = threadIdx.x; e < R * D; e += 64 * kStreamWaves) sBV[e] = bf16_to_f32(bv[(int64_t)(e / D) * n + (e % D)]);
+    if (use_res) {
+        const uint16_t *bv = p.lora_b + ((int64_t)ad * 2 + 1) * R * n + (int64_t)h * D;
+        for (int e = threadIdx.x; e < R * D; e += 64 * kStreamWaves) sBV[e] = bf16_to_f32(bv[(int64_t)(e / D) * n + (e % D)]);
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
+        for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-                for (int t = 0; t < RT; ++t)
+            for (int t = 0; t < RT; ++t)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int rho = 16 * t + 4 * grp + i;
-                        if (rho < R) sAcc[(wave * ROWS_PER_WAVE + nt * 16 + col) * R + rho] = racc[t][nt][i];
-                    }
-            __syncthreads();
+                for (int i = 0; i < 4; ++i) sAcc[(wave * ROWS_PER_WAVE + nt * 16 + col) * R + 16 * t + 4 * grp + i] = racc[t][nt][i];
+        __syncthreads();
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                const float *ar = sAcc + (wave * ROWS_PER_WAVE + nt * 16 + col) * R;
+        for (int nt = 0; nt < 2; ++nt) {
+            const float *ar = sAcc + (wave * ROWS_PER_WAVE + nt * 16 + col) * R;
 #pragma unroll 4
-                for (int rho = 0; rho < R; ++rho) {
-                    const float c = ar[rho];
+            for (int rho = 0; rho < R; ++rho) {
+                const float c = ar[rho];
 #pragma unroll
-                    for (int mt = 0; mt < 8; ++mt)
+                for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) oacc[mt][nt][i] += c * sBV[rho * D + 16 * mt + 4 * grp + i];
-                }
+                    for (int i = 0; i < 4; ++i) oacc[mt][nt][i] += c * sBV[rho * D + 16 * mt + 4 * grp + i];
             }
         }
     }
@@ -605,6 +590,11 @@ hipError_t dispatch_prefill(int r, const PrefillArgs &pa, hipStream_t st, void *
 //    the compute units (4 agents x 250 rows over 32K, 8B heads, rank 16, RoPE off: 112 workgroups
 //    920 us, 224 workgroups 844 us, both before the copies went further ahead; now 620) and at
 //    rank 64 (RoPE off), where eight waves spill (4 agents x 2048 rows: 8.4 -> 7.5 ms).
+// Against the kernel that the pipelined one replaced (two barriers per tile, now the rebuild kernel alone),
+// 8B heads, us before / now, of 8 agents x 1024 rows over 8K, 4 x 129..250 over 16K and 12 x 300..600 over
+// 100 tokens: RoPE off, rank 8 1670 / 1431, 698 / 328, 131 / 126; 16 1656 / 1449, 691 / 316, 137 / 136; 32
+// 1926 / 1609, 803 / 363, 177 / 166; 64 2460 / 2263, 1006 / 437, 274 / 245; RoPE on, rank 8 2033 / 1709, 859 / 477,
+// 147 / 142; 16 2000 / 1725, 846 / 469, 150 / 146; rank 32 of the small grids 912 / 507; no adapter 1308 / 1042.
 // An (agent, KV head) pair keeps to one XCD, whose 32 compute units hold one workgroup each, so the
 // grid is small when the XCD with the most pairs is at most half full (one KV head, 12 agents x 600
 // rows over 6000, RoPE on: 40 workgroups of 128 rows on four of the XCDs, two rounds, against 20 of

@@ -34,8 +34,7 @@ __device__ __forceinline__ void poison_unreached_rows(const PrefillArgs &p, int 
     }
 }
 
-// Launches of the pipelined kernel (prefill_stream.hip) with 128 or 256 query rows per workgroup
-// and of the in-place rebuild kernel (prefill.hip).
+// Launch of the pipelined kernel (prefill_stream.hip) with 128 or 256 query rows per workgroup.
 hipError_t launch_stream(int r, int g, bool rope, bool rows128, const PrefillArgs &pa, hipStream_t st, void *const *ev);
 
 }  // namespace fkvp

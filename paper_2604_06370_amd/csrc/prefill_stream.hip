@@ -60,10 +60,11 @@ constexpr float kLazyRescale = 8.f;
 // ring of its own.
 template <int R, bool ROPE>
 struct Ring {
+    static_assert(!(ROPE && R >= 64), "rank 64 with RoPE runs on the rebuild kernel");
     static constexpr int RT = R == 0 ? 0 : (R + 15) / 16;
     static constexpr int NRB = (RT + 1) / 2;             // 32-row blocks of the rank accumulator
     static constexpr bool CSPLIT = R >= 32;
-    static constexpr int KR = (ROPE ? R < 64 : R <= 16) ? 4 : 3;
+    static constexpr int KR = ROPE || R <= 16 ? 4 : 3;
     static constexpr int VR = (ROPE ? R >= 32 : R >= 64) ? 2 : (!ROPE && R <= 16 ? 4 : 3);
     static constexpr int KAHEAD = ROPE ? KR - 2 : KR - 1, VAHEAD = VR - 1;  // iterations from request to use
     static constexpr int CPAGE = RT * 1024;
