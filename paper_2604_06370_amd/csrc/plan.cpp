@@ -251,9 +251,9 @@ fkv_status fkv_decode_plan_create(const fkv_decode_plan_params *prm, const int32
         // that gives the two resident workgroups per compute unit few rounds (16 agents over
         // a 32K prefix: 1152 workgroups; 16 to 64 pages within 12 %, 32 best); on larger
         // workloads items of 64 or 128 pages, the largest that still leave at least 2.5
-        // workgroups per resident slot: fewer B_K^T builds and partial rows per page (64
-        // agents over a 128K tree: 2978 -> 2743 us per step at 128 pages; 70B heads, 24
-        // agents: 727 -> 637 us).
+        // workgroups per resident slot: fewer B_K^T builds and partial rows per page (items
+        // of 32, 64 and 128 pages: 64 agents over a 128K tree 2174, 1954 and 1864 us per call; 70B
+        // heads, 24 agents 342, 309 and 296, of which the rule takes 64).
         int32_t rope_pages = 32;
         if (rope) {
             auto rope_blocks = [&](int32_t pages) {

@@ -13,8 +13,8 @@
 // and at the end O = (O + acc_r . B_V[h]) / l (Eq. 4) is written in bf16.
 //
 // What bounds it, and the forms that follow from it (16 agents x 2048 rows over 32K, 8B heads,
-// rank 16, unless another size is named; the matrix cores are busy 51 % of the launch, whose clock
-// power holds at 1.83 GHz, against 41 % of the kernel before, 27.7 ms):
+// rank 16, unless another size is named; the matrix cores are busy 48 % of the launch at 1.94 GHz,
+// 66 % at 1.64 GHz without RoPE, 20.1 ms, where power holds the clock; the kernel before: 41 %, 27.7 ms):
 //  - One iteration works on three tiles: value products of tile t - 1 beside the row maxima of tile
 //    t, then scores of tile t + 1 beside the weights of tile t, so that a wave always has matrix
 //    and vector work that do not wait for each other; one barrier per tile.  The order is written
