@@ -29,16 +29,17 @@ double item_page_cost(int32_t agents) { return 1.0 + 0.095 * (double)agents; }
 constexpr double kItemOverhead = 24.0;
 // Decode with RoPE at ranks 32 and 64: whether a plan takes waves of twice the agents
 // (decode_rope_wave_agents).  `all` counts the pages that narrow waves walk, over items and KV heads,
-// `saved` those that wide waves would not.  Measured over 590 plans (one and eight KV heads, four and
+// `saved` those that wide waves would not.  Measured over 687 plans (one and eight KV heads, four and
 // eight query heads each, 1 to 64 agents, 500 to 131072 shared tokens), times of the wide form in
 // those of the narrow one by the pages saved per compute unit: below 48, 0.88 to 1.27 (6 agents over
-// 500 tokens at rank 32, 13.5 -> 17.2 us; 12 over 40000 at one KV head 1.16); 48 to 64, 0.89 to 1.05; 64
-// to 130, 0.86 to 1.01; 400 and more, 0.73 to 0.86 (64 agents over a 128K tree at rank 32, 2243 -> 1929 us;
-// 24 with 70B heads at rank 64, 361 -> 305).  An item of one agent has nothing to save and takes up to
-// 4 % longer (24 agents of 1000 to 8000 tokens alone, rank 64: 117 -> 122 us), so at least an eighth of
-// the pages has to go.
-constexpr int64_t kWideSavedPages = 48;
-bool rope_wide_pays(int64_t all, int64_t saved, int64_t cus) { return saved >= kWideSavedPages * cus && 8 * saved >= all; }
+// 500 tokens at rank 32, 13.5 -> 17.2 us; 12 over 40000 at one KV head 1.16); 48 to 64, 0.89 to 1.02 with
+// eight KV heads and 0.95 to 1.05 with one; 64 to 130, 0.86 to 1.01; 400 and more, 0.73 to 0.86 (64 agents
+// over a 128K tree at rank 32, 2243 -> 1929 us; 24 with 70B heads at rank 64, 361 -> 305).  An item of one
+// agent has nothing to save and takes up to 4 % longer (24 agents of 1000 to 8000 tokens alone, rank
+// 64: 117 -> 122 us), so at least an eighth of the pages has to go.
+bool rope_wide_pays(int64_t all, int64_t saved, int32_t hkv, int64_t cus) {
+    return saved >= (hkv >= 8 ? 48 : 64) * cus && 8 * saved >= all;
+}
 }
 
 extern "C" {
@@ -115,7 +116,7 @@ fkv_status fkv_decode_plan_create(const fkv_decode_plan_params *prm, const int32
                 saved += s.n * (n - (c + wide - 1) / wide);
             }
         const int64_t cus = prm->num_cus > 0 ? prm->num_cus : 256;
-        ag = rope_wide_pays(all * prm->hkv, saved * prm->hkv, cus) ? wide : narrow;
+        ag = rope_wide_pays(all * prm->hkv, saved * prm->hkv, prm->hkv, cus) ? wide : narrow;
     }
 
     // 2. agent chunks per segment: up to item_agents agents, in whole groups of ag where

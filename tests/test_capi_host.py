@@ -496,13 +496,13 @@ def test_prefill_form_counts_the_fullest_xcd():
                                                   (64, 8, 32, 2, 2), (32, 8, 16, 4, 4), (64, 8, 8, 2, 2)])
 def test_decode_plan_takes_wide_waves_where_they_save_enough(hq, hkv, r, narrow, wide):
     """RoPE on at ranks 32 and 64: waves of twice the agents where 48 or more page visits per compute
-    unit go, none for small or private contexts.  Narrow plans are those that the page rules were
+    unit go (64 below eight KV heads), none for small or private contexts.  Narrow plans are those that the page rules were
     measured on: three wave groups are split 2 + 1, items of more than one group spread over every
     compute unit."""
     agents = 16
     groups = min(agents, rt.decode_plan_default_agents(hq, hkv, r, True)) // narrow  # per full item
     per_page = hkv * (agents // (groups * narrow)) * (groups - groups * narrow // wide)  # visits saved per shared page
-    edge = -(-48 * 256 // per_page) if per_page else 5000
+    edge = -(-(48 if hkv >= 8 else 64) * 256 // per_page) if per_page else 5000
 
     def plan(n, shared, private, **kw):
         bb, sl = _fanout_tables(n, shared, [private] * n)
