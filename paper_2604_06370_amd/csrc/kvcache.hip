@@ -311,7 +311,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(ScatterArgs a) {
 // kinds of workgroups:
 //  - shrink (one per four pages, or one per page, see one_page_shrink): wave w covers every fourth block of the hidden dimension with 16x16x32
 //    products (16 bytes of one token's x row and of one row of A per lane, A L2-resident),
-//    eight k-steps of loads in flight; the four partial tiles are summed through LDS.  C_K is
+//    two rounds of one or two k-steps of loads in flight; the four partial tiles are summed through LDS.  C_K is
 //    computed transposed (A as the row operand), so each lane holds 4 ranks of one token
 //    and C_V 4 tokens of one rank: both are 8 contiguous bytes of the residual page;
 //  - base (one per page and pair of KV heads): the page's 16 token rows of K and V of
@@ -338,8 +338,8 @@ constexpr int kProdChunk = 1024;  // hidden is a multiple of this (four waves x 
 constexpr int kProdHeads = 2;     // KV heads per base workgroup
 constexpr int kShrinkPages = 4;   // pages (16-token tiles) per shrink workgroup of long sequences
 // One page per shrink workgroup where no sequence of the call has more than eight (decode steps, short
-// chunks): such a call is a chain of memory latencies, and one page's registers hold four times the steps
-// in flight (4 sequences at hidden 4096, four pages and one: 64 tokens, rank 16, 25.9 / 13.5 us; rank 64,
+// chunks): such a call is a chain of memory latencies, and one page's registers hold two to four times the
+// steps in flight (4 sequences at hidden 4096, four pages and one: 64 tokens, rank 16, 25.9 / 13.5 us; rank 64,
 // 48.1 / 34.7; 9 tokens, rank 32, 23.4 / 19.1; one token as many us or up to a quarter fewer).  Longer sequences
 // decide for the call, as they set its time (16 of 1 to 2000 tokens: up to 13 % longer with one page for
 // the short ones among them).  At rank 64 a workgroup takes half of a compute unit, so that a full launch of
